@@ -31,9 +31,10 @@ PEAK_HBM_GBS = 8000.0
 
 # The translation unit of the dominant kernel (the hidden conv layer): its
 # source and every header it includes.
-KERNEL_SOURCES = ("paper_2604_12841_amd/csrc/conv_hidden.hip", "paper_2604_12841_amd/csrc/tiles.h",
-                  "paper_2604_12841_amd/csrc/activation.h", "paper_2604_12841_amd/csrc/internal.h",
-                  "include/predecoder.h")
+KERNEL_SOURCES = ("paper_2604_12841_amd/csrc/conv_hidden_wide_bf16.hip",
+                  "paper_2604_12841_amd/csrc/conv_hidden_kernel.h", "paper_2604_12841_amd/csrc/conv_hidden.h",
+                  "paper_2604_12841_amd/csrc/tiles.h", "paper_2604_12841_amd/csrc/activation.h",
+                  "paper_2604_12841_amd/csrc/internal.h", "include/predecoder.h")
 
 
 def kernel_source_hash():

@@ -1,0 +1,18 @@
+// conv_hidden_head_bf16.hip -- instances of the hidden kernel: a fused 1x1x1 head, bf16.
+#include "conv_hidden_kernel.h"
+
+namespace pd {
+
+template <>
+hipError_t launch_hidden_head<false>(const HiddenCall& c) {
+  constexpr bool F8 = false;
+  PD_HIDDEN_CASE(64, 64, EPI_HEAD)
+  PD_HIDDEN_CASE(128, 128, EPI_HEAD)
+  PD_HIDDEN_CASE(64, 128, EPI_HEAD)
+  PD_HIDDEN_CASE(128, 64, EPI_HEAD)
+  PD_HIDDEN_CASE(64, 32, EPI_HEAD)  // the head layer in 32-channel slices (small batches)
+  PD_HIDDEN_CASE(128, 32, EPI_HEAD)
+  return hipErrorInvalidValue;
+}
+
+}  // namespace pd
