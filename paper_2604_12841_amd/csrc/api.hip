@@ -61,7 +61,7 @@ struct pd_predecoder {
   Tiling tiling{};               // shared by every k x k x k layer (bf16 and fp8 paths)
   Workspace ws;                  // sized for max_batch
   int32_t* tables = nullptr;
-  std::vector<void*> wdev;       // per conv layer: fragments (bf16) or [tap][ci][co] (fp32)
+  std::vector<void*> wdev;       // per conv layer: fragments
   std::vector<size_t> wslice;    // per conv layer: bytes of the fragments of one 128-channel slice of a
                                  // 256-wide layer (run as two slices), 0 otherwise
   std::vector<float*> bdev;      // per conv layer: bias fp32 (a 3x3x3 output layer: [4] biases, [4] scales)
@@ -888,11 +888,12 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
     const pd_layer& L = h->layers[l];
     const int row_bytes = L.c_out * (fp32 ? 4 : aelem);
     if ((s = prepare_rows(ws, l & 1, row_bytes, st)) != PD_OK) return s;
-    const bool head_layer = !fp32 && !out3 && l == n - 2;  // carries the head unless the run stops at it
+    const bool head_layer = !out3 && l == n - 2;  // carries the head unless the run stops at it
     const bool fuse_head = head_layer && stop < 0;
     if (fp32) {
       s = check_launch(pd::launch_conv_fp32(g, L.c_in, L.c_out, L.act, (const float*)x, (float*)y,
-                                            (const float*)h->wdev[l], h->bdev[l], batch, st));
+                                            (const float*)h->wdev[l], h->bdev[l], fuse_head ? 1 : 0, h->head_w,
+                                            h->head_b, h->tables, ws.nib, logits, batch, h->n_cu, st));
     } else if (l == 0 && fuse_head && L.c_in == 2) {  // one hidden layer: layer 1 carries the head
       s = check_launch(pd::launch_conv_single(g, tl, L.c_out, L.act, x, h->wdev[l], h->bdev[l], h->head_w,
                                               h->head_b, h->tables, ws.nib, logits, batch, h->n_cu, st));
@@ -941,6 +942,7 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
       }
       head_done = fuse_head && l > 0;
     }
+    if (fp32) head_done = fuse_head;
     if (s != PD_OK) return s;
     if (l == stop) {
       at->buf = y;
@@ -959,9 +961,9 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
     const pd_layer& L = h->layers[n - 1];
     s = run_hidden(h, ws, tl, L.c_in, L.c_out, 1, L.act, x, nullptr, 0, h->wdev[n - 1], h->bdev[n - 1], 2, nullptr,
                    nullptr, logits, batch, fp8, nullptr, 0, ks, st);
-  } else if (!head_done) {  // fp32, or a one-hidden-layer network on the paper's layout
-    s = check_launch(pd::launch_head(g, h->layers[n - 1].c_in, fp32, x, h->head_w, h->head_b, h->tables,
-                                     ws.nib, logits, batch, st));
+  } else if (!head_done) {  // a one-hidden-layer network on the paper's layout
+    s = check_launch(pd::launch_head(g, h->layers[n - 1].c_in, x, h->head_w, h->head_b, h->tables, ws.nib, logits,
+                                     batch, st));
   }
   if (s != PD_OK) return s;
   if ((s = mark()) != PD_OK) return s;
@@ -1219,11 +1221,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
       }
       s = upload(&wd, f.data(), f.size() * 2);
     } else {
-      std::vector<float> r((size_t)27 * L.c_in * L.c_out);
-      for (int co = 0; co < L.c_out; ++co)
-        for (int ci = 0; ci < L.c_in; ++ci)
-          for (int tap = 0; tap < 27; ++tap)
-            r[((size_t)tap * L.c_in + ci) * L.c_out + co] = w[((size_t)co * L.c_in + ci) * 27 + tap];
+      std::vector<float> r = pd::conv_fp32_fragments(w, L.c_in, L.c_out);
       s = upload(&wd, r.data(), r.size() * 4);
     }
     h->wdev.push_back(wd);

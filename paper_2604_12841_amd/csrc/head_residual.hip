@@ -7,7 +7,9 @@
 // at data qubits (grid sites (r, c), r, c < d), channel 2 where an X
 // stabilizer sits (or is drawn, in the paper's layout), channel 3 likewise
 // for Z.  The four flip bits of a voxel are kept as one nibble per voxel in a
-// small workspace; fp32 logits are written only when asked for.
+// small workspace; fp32 logits are written only when asked for.  (Used by
+// one-hidden-layer bf16 networks on the paper's layout; elsewhere the head is
+// fused into the last hidden layer.)
 //
 // K5 (residual + repack): a wave64 builds one packed 64-bit output word at a
 // time from nibble rows staged in LDS.  Lane l computes bit 64 w + l of
@@ -24,7 +26,6 @@ namespace pd {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-template <bool FP32>
 __global__ void __launch_bounds__(256) head_kernel(Geom g, int cin, const void* __restrict__ x,
                                                    const float* __restrict__ w_head,
                                                    const float* __restrict__ b_head,
@@ -43,27 +44,18 @@ __global__ void __launch_bounds__(256) head_kernel(Geom g, int cin, const void* 
   const int i = s / g.H, j = s - i * g.H;
   const long long p = padded_index(g, b, t, i, j);
   float acc[4] = {b_head[0], b_head[1], b_head[2], b_head[3]};
-  if (FP32) {
-    const float* xr = reinterpret_cast<const float*>(x) + p * cin;
-    for (int c = 0; c < cin; ++c) {
-      float xv = xr[c];
+  const u32x4* xr = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(x) + p * cin);
+  for (int c8 = 0; c8 < cin / 8; ++c8) {
+    u32x4 q = xr[c8];
 #pragma unroll
-      for (int o = 0; o < 4; ++o) acc[o] = fmaf(w[o * cin + c], xv, acc[o]);
-    }
-  } else {
-    const u32x4* xr = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(x) + p * cin);
-    for (int c8 = 0; c8 < cin / 8; ++c8) {
-      u32x4 q = xr[c8];
+    for (int h = 0; h < 4; ++h) {
+      float lo = __uint_as_float(q[h] << 16);
+      float hi = __uint_as_float(q[h] & 0xffff0000u);
+      const int c = c8 * 8 + 2 * h;
 #pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        float lo = __uint_as_float(q[h] << 16);
-        float hi = __uint_as_float(q[h] & 0xffff0000u);
-        const int c = c8 * 8 + 2 * h;
-#pragma unroll
-        for (int o = 0; o < 4; ++o) {
-          acc[o] = fmaf(w[o * cin + c], lo, acc[o]);
-          acc[o] = fmaf(w[o * cin + c + 1], hi, acc[o]);
-        }
+      for (int o = 0; o < 4; ++o) {
+        acc[o] = fmaf(w[o * cin + c], lo, acc[o]);
+        acc[o] = fmaf(w[o * cin + c + 1], hi, acc[o]);
       }
     }
   }
@@ -264,17 +256,12 @@ __global__ void __launch_bounds__(256) residual_from_flips_kernel(Geom g, const 
   if (lane == 0) residual[(long long)b * g.Wd + w] = m;
 }
 
-hipError_t launch_head(const Geom& g, int cin, int fp32, const void* x, const float* w_head,
-                              const float* b_head, const int32_t* tables, uint8_t* nib, float* logits,
-                              int batch, hipStream_t stream) {
+hipError_t launch_head(const Geom& g, int cin, const void* x, const float* w_head, const float* b_head,
+                       const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream) {
   long long total = (long long)batch * g.V;
   unsigned grid = (unsigned)((total + 255) / 256);
-  if (fp32)
-    hipLaunchKernelGGL(head_kernel<true>, dim3(grid), dim3(256), 0, stream, g, cin, x, w_head, b_head,
-                       tables, nib, logits, batch);
-  else
-    hipLaunchKernelGGL(head_kernel<false>, dim3(grid), dim3(256), 0, stream, g, cin, x, w_head, b_head,
-                       tables, nib, logits, batch);
+  hipLaunchKernelGGL(head_kernel, dim3(grid), dim3(256), 0, stream, g, cin, x, w_head, b_head, tables, nib, logits,
+                     batch);
   return hipGetLastError();
 }
 

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/predecoder.h"
 
 namespace pd {
@@ -274,12 +276,20 @@ __host__ __device__ inline long long conv_workgroups(long long ntiles, long long
   return n < cap ? n : cap;
 }
 
-hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const float* x, float* y,
-                            const float* w, const float* bias, int batch, hipStream_t stream);
+// A 3x3x3 layer in fp32: c_in = 2 or a multiple of 8 up to 128, c_out a
+// multiple of 8 up to 128, x and y rows of c_in / c_out floats in the
+// zero-halo layout (pad 1), w the fragments of conv_fp32_fragments.  head:
+// the last hidden layer, whose epilogue applies the 1x1x1 head (head_w
+// [4][c_out]) and the threshold instead of writing y.
+hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const float* x, float* y, const float* w,
+                            const float* bias, int head, const float* head_w, const float* head_b,
+                            const int32_t* tables, uint8_t* nib, float* logits, int batch, int n_cu,
+                            hipStream_t stream);
+std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout);
 
-hipError_t launch_head(const Geom& g, int cin, int fp32, const void* x, const float* w_head,
-                       const float* b_head, const int32_t* tables, uint8_t* nib, float* logits,
-                       int batch, hipStream_t stream);
+// The 1x1x1 head and the threshold over bf16 activation rows of c_in values.
+hipError_t launch_head(const Geom& g, int cin, const void* x, const float* w_head, const float* b_head,
+                       const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream);
 
 hipError_t launch_residual_pack(const Geom& g, const int32_t* tables, const uint64_t* det,
                                 const uint8_t* nib, uint64_t* flips, uint64_t* residual, int batch,
