@@ -214,7 +214,7 @@ float bf16_value(float f) {
 
 // Tiling plan for the 3x3x3 layers: the candidate with the fewest MFMA rows
 // per sample whose double-buffered 32-channel staging fits in LDS (cost 2 x
-// rows; ties go to per-sample tiles, then boxes of 16-voxel rows, then the
+// rows; ties go to per-sample tiles, then cells of 16-voxel rows, then the
 // smaller span).
 
 long long flat_span(const Geom& g, long long seg_len, long long nseg, int batch) {
@@ -238,8 +238,27 @@ long long flat_span(const Geom& g, long long seg_len, long long nseg, int batch)
   return best;
 }
 
+// The most lines a tile of a cell of n voxels stages (cell line space, see
+// pd::Tiling); limit + 1 when over `limit`.  Tiles repeat their place in the
+// cell's rounds after at most BI BJ of them.
+int cell_span(const Tiling& t, int n, int pad, int limit) {
+  const int bij = t.BI * t.BJ;
+  const int halo = 2 * pad * (t.sa + t.sb + 1) + 1;
+  if (n >= pd::kTileRows && halo + pd::kTileRows - 1 > limit) return limit + 1;  // most cells: no need to look closer
+  auto line = [&](int u) {
+    const int r = u % bij;
+    return u / bij * t.sa + r / t.BJ * t.sb + r % t.BJ;
+  };
+  int best = 0;
+  for (int k = 0; k < std::min(t.ntT, bij) && best <= limit; ++k) {
+    const int u0 = k * pd::kTileRows, u1 = std::min(u0 + pd::kTileRows, n) - 1;
+    best = std::max(best, line(u1) - line(u0) + halo);
+  }
+  return std::min(best, limit + 1);
+}
+
 Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
-  // 5x5x5 layers: their own (larger) staging buffers, box tiles on a halo of two
+  // 5x5x5 layers: their own (larger) staging buffers, cells on a halo of two
   const int kMaxSpan = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                : pd::conv_hidden_max_span(5);
   const int p = g.pad;
@@ -278,26 +297,23 @@ Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
     t.span = (int)std::min<long long>(flat_span(g, (long long)nb * g.V, 1, nb), 1 << 30);
     consider(t, 2ll * g.V + 2);  // +2: prefer per-sample tiles at equal cost
   }
-  // boxes
-  for (int BJ = 1; BJ <= std::min(g.H, 256); ++BJ)
-    for (int BI = 1; BI <= std::min(g.H, 256 / BJ); ++BI) {
-      int BT = std::min(g.T, 256 / (BI * BJ));
-      if (BT < 1) continue;
+  // cells
+  for (int BJ = 1; BJ <= g.H; ++BJ)
+    for (int BI = 1; BI <= g.H; ++BI) {
       Tiling t{};
       t.mode = 1;
-      t.BT = BT;
       t.BI = BI;
       t.BJ = BJ;
-      t.ntT = (g.T + BT - 1) / BT;
+      t.ntT = (g.T * BI * BJ + pd::kTileRows - 1) / pd::kTileRows;
       t.ntI = (g.H + BI - 1) / BI;
       t.ntJ = (g.H + BJ - 1) / BJ;
       t.sa = (BI + 2 * p) * (BJ + 2 * p);
       t.sb = BJ + 2 * p;
-      t.span = (BT + 2 * p) * (BI + 2 * p) * (BJ + 2 * p);
-      // (a box row of BJ < 16 voxels, whose 16-lane LDS reads span two staged
-      // lines, costs little: at d = T = 25 a 5x3x16 box and a 9x13x2 box
-      // reach 0.54 and 0.53 of peak per MFMA row, so the row count decides,
-      // and BJ = 16 only breaks ties)
+      t.span = cell_span(t, g.T * BI * BJ, p, kMaxSpan);
+      // (a cell row of BJ < 16 voxels, whose 16-lane LDS reads span two
+      // staged lines, costs little: at d = T = 25 a 5x3x16 box and a 9x13x2
+      // box reached 0.54 and 0.53 of peak per MFMA row, so the row count
+      // decides, and BJ = 16 only breaks ties)
       const long long rows = (long long)t.ntT * t.ntI * t.ntJ * pd::kTileRows;
       consider(t, 2 * rows + (BJ % 16 != 0));
     }

@@ -18,7 +18,7 @@ hipError_t launch_conv_hidden(const Geom& g, const Tiling& tl, int cin, int cout
   if (tl.span <= 0 || tl.span > conv_hidden_max_span(ks)) return hipErrorInvalidValue;
   // a shortcut projected in the epilogue: from at most 8 channels of sc
   if (head == 4 && head_w && (!head_b || !sc || sc_stride < 1 || sc_stride > 8)) return hipErrorInvalidValue;
-  // the halo holds every tap: a 5x5x5 layer needs the two-voxel halo (and box tiles)
+  // the halo holds every tap: a 5x5x5 layer needs the two-voxel halo (and cells)
   if ((ks - 1) / 2 > g.pad || (tl.mode == 0 && g.pad != 1)) return hipErrorInvalidValue;
   // parts per tile: a power of two dividing the layer's chunks, with room
   // for every unit's sums

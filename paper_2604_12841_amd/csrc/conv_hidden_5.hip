@@ -1,5 +1,5 @@
 // conv_hidden_5.hip -- instances of the hidden kernel: 5x5x5 layers (Model 3
-// of Table models; bf16, box tiles only), the output layer included.
+// of Table models; bf16, cell tiles only), the output layer included.
 #include "conv_hidden_kernel.h"
 
 namespace pd {

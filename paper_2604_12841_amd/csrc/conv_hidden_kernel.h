@@ -229,7 +229,7 @@ __host__ __device__ inline uint32_t stage_offset(const Geom& g, const Tiling& tl
                                                  long long base, long long limit, int span, int k, int tid) {
   const int q = k * NT + tid;
   const int vv = stage_voxel(q);
-  const long long gv = staged_voxel_fast<MODE>(g, tl, src, vv, limit);
+  const long long gv = staged_voxel<MODE>(g, tl, src, vv, limit);
   return (vv < span && gv >= 0) ? (uint32_t)((gv - base) * ROW + stage_gran(q) * 16) : kNoVoxel;
 }
 
@@ -303,7 +303,7 @@ __device__ __forceinline__ void shortcut_of(const uint16_t* __restrict__ sc, int
 
 // F8: E4M3 activations and weights (bias holds [COUT] biases then [COUT]
 // per-channel weight scales; y and x hold one byte per value).  KS: the
-// kernel size, 3 or 5 (5: box tiles on a halo of two).
+// kernel size, 3 or 5 (5: cells on a halo of two).
 template <int CIN, int COUT, int EPI, int MODE, bool F8, int KS>
 __global__ void __launch_bounds__(NT)
 __attribute__((amdgpu_waves_per_eu(Conv<KS>::WG_PER_CU, Conv<KS>::WG_PER_CU)))
@@ -314,7 +314,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
                    float* __restrict__ logits, int batch, int kshift_arg, float* __restrict__ partial,
                    const uint16_t* __restrict__ sc, int sc_stride, int lsl, uint32_t* __restrict__ sched,
                    int nstat) {
-  static_assert(KS == 3 || MODE == 1, "5x5x5 layers run on box tiles");
+  static_assert(KS == 3 || MODE == 1, "5x5x5 layers run on cell tiles");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using W = Split<COUT>;
   using L = Lds<COUT, KS>;
@@ -1089,7 +1089,7 @@ hipError_t launch_hidden(const Geom& g, const Tiling& tl, int act, const void* x
   const long long nunits = tl.ntiles << (kshift + lsl);
   const long long nwg = conv_workgroups(nunits, n_workgroups);
   if (nunits <= 2 * nwg) sched = nullptr;  // every unit is one of the two fixed ones
-  // fixed units per workgroup before the counters: two on box tiles; on flat
+  // fixed units per workgroup before the counters: two on cells; on flat
   // tiles seven eighths of a workgroup's share
   const long long share = (nunits + 7) / 8 / (nwg / 8);
   const int nstat = tl.mode == 0 ? (int)std::max(2ll, share * 7 / 8) : 2;

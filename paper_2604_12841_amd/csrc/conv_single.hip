@@ -66,10 +66,12 @@ struct Lds {
 
 // Both channels (4 bytes) of staged voxel NT k + tid (voxel 0, a zero halo
 // voxel, past the footprint).
+template <int MODE>
 __device__ __forceinline__ uint32_t plane_load(const Geom& g, const Tiling& tl, const uint32_t* __restrict__ planes,
                                                const StageSrc& src, long long limit, int k, int tid) {
   const int vv = k * NT + tid;
-  return planes[staged_voxel(g, tl, src.origin, src.bo, vv < tl.span ? vv : 0, limit)];
+  const long long p = staged_voxel<MODE>(g, tl, src, vv, limit);
+  return planes[vv < tl.span && p >= 0 ? p : 0];
 }
 
 template <int COUT, int MODE>
@@ -110,7 +112,7 @@ __global__ void __launch_bounds__(NT) conv_single_kernel(Geom g, Tiling tl, int 
     const StageSrc src = source_of(tile);
 #pragma unroll
     for (int k = 0; k < PLANE_RMAX; ++k)
-      *(lds_u32_w*)(lds + (k * NT + tid) * 4) = plane_load(g, tl, planes, src, limit, k, tid);
+      *(lds_u32_w*)(lds + (k * NT + tid) * 4) = plane_load<MODE>(g, tl, planes, src, limit, k, tid);
   }
   // This wave's weight fragments (4 k-steps of its 32 channels): the same
   // for every tile.
@@ -138,7 +140,7 @@ __global__ void __launch_bounds__(NT) conv_single_kernel(Geom g, Tiling tl, int 
     // next tile's planes into registers while this tile computes
     uint32_t nxt[PLANE_RMAX];
 #pragma unroll
-    for (int k = 0; k < PLANE_RMAX; ++k) nxt[k] = plane_load(g, tl, planes, next_src, limit, k, tid);
+    for (int k = 0; k < PLANE_RMAX; ++k) nxt[k] = plane_load<MODE>(g, tl, planes, next_src, limit, k, tid);
 
     lds_u32* const a32 = (lds_u32*)(lds + gbuf * ABUF);
     f32x16 acc[MB];

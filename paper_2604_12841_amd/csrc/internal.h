@@ -57,9 +57,16 @@ __host__ __device__ inline long long padded_index(const Geom& g, int b, int t, i
 //    that falls on one reads a zero region instead.  The staged span runs
 //    from u(first row) - (PU + H + 1) to u(last row) + (PU + H + 1).
 //    (Mode 0 needs pad = 1.)
-//  mode 1 (box): a BT x BI x BJ box of (t, i, j); the staged input is the
-//    (BT+2 pad) x (BI+2 pad) x (BJ+2 pad) padded box around it, halo
-//    included.
+//  mode 1 (cells): the grid is cut into cells of BI x BJ sites (the last of
+//    a row or column of cells may reach past the grid), and a tile is 256
+//    consecutive voxels of one cell in (t, i, j) order: it starts and ends
+//    anywhere in a round of the cell, so only a cell's last tile has idle
+//    rows.  (Boxes of whole rounds of a cell, the form before, left 10-18 %
+//    of the rows idle at d = 17-29.)  The staged input lives in the cell's
+//    padded line space, halo included: voxel (a, c, e) of the (T + 2 pad) x
+//    (BI + 2 pad) x (BJ + 2 pad) box has line index a sa + c sb + e, and a
+//    tile stages the lines from its first row's (0,0,0) tap to its last
+//    row's last tap.
 // In both modes the LDS voxel of row r for tap (dt, di, dj) in {0..k-1}^3 is
 // row_base(r) + dt * sa + di * sb + dj.
 // Division by a runtime constant d >= 2 for numerators n < 2^31:
@@ -96,11 +103,12 @@ struct Tiling {
   int mode;
   long long seg_len;
   int tiles_per_seg;
-  int BT, BI, BJ, ntT, ntI, ntJ;
+  int BI, BJ;         // mode 1: sites of a cell
+  int ntT, ntI, ntJ;  // mode 1: tiles per cell, cells per column and row of the grid
   int sa, sb;
   int span;      // staged voxels per tile (upper bound), sizes the LDS buffers
   long long ntiles;
-  FastDiv div_a, div_b;  // staging decode: mode 0 by PU and H; mode 1 by (BI+2)(BJ+2) and BJ+2
+  FastDiv div_a, div_b;  // staging decode: by sa and sb
   // tile and row decoding (tiles.h): mode 0 by tiles_per_seg, V, H^2 and H;
   // mode 1 by the tiles per sample, ntI ntJ, ntJ, BI BJ and BJ
   FastDiv dv_tps, dv_V, dv_HH, dv_H, dv_per, dv_ntij, dv_ntj, dv_bij, dv_bj;
@@ -188,7 +196,7 @@ struct Split_k {
   uint32_t* sched = nullptr;
 };
 
-// ks: kernel size 3, or 5 (box tiles, a halo of two; bf16 c_in / c_out of
+// ks: kernel size 3, or 5 (cell tiles, a halo of two; bf16 c_in / c_out of
 // 64 or 128, activations and the output layer).
 hipError_t launch_conv_hidden(const Geom& g, const Tiling& tl, int cin, int cout, int act, const void* x,
                               void* y, int ystride, const void* wfrag, const float* bias, int head,

@@ -7,6 +7,34 @@
 
 namespace pd {
 
+// Cell-mode (mode 1) tile: its sample, run number within the cell, and the
+// cell's first grid row and column.
+struct CellTile {
+  int b, run, i0, j0;
+};
+
+__host__ __device__ inline CellTile cell_tile(const Tiling& tl, int tile) {
+  const int per = tl.ntT * tl.ntI * tl.ntJ, ntij = tl.ntI * tl.ntJ;
+  CellTile ct;
+  ct.b = (int)fdiv((uint32_t)tile, tl.dv_per);
+  const int rem = tile - ct.b * per;
+  ct.run = (int)fdiv((uint32_t)rem, tl.dv_ntij);
+  const int rem2 = rem - ct.run * ntij;
+  const int ti = (int)fdiv((uint32_t)rem2, tl.dv_ntj);
+  ct.i0 = ti * tl.BI;
+  ct.j0 = (rem2 - ti * tl.ntJ) * tl.BJ;
+  return ct;
+}
+
+// Voxel u of a cell, in (t, i, j) order: its round, row and column in the cell.
+__host__ __device__ inline void cell_voxel(const Tiling& tl, int u, int* a, int* c, int* e) {
+  const int bij = tl.BI * tl.BJ;
+  *a = (int)fdiv((uint32_t)u, tl.dv_bij);
+  const int r = u - *a * bij;
+  *c = (int)fdiv((uint32_t)r, tl.dv_bj);
+  *e = r - *c * tl.BJ;
+}
+
 // Row r (0..255) of tile `tile`: false if the row is outside the volume,
 // else its padded output index (pidx) and its column j (col).  Also the LDS
 // voxel of the row's (0,0,0) tap (lds_base) and the staging origin: the
@@ -44,22 +72,17 @@ __host__ __device__ inline bool tile_row(const Geom& g, const Tiling& tl, int ti
     if (col) *col = j;
     return true;
   } else {
-    const int per = tl.ntT * tl.ntI * tl.ntJ, ntij = tl.ntI * tl.ntJ;
-    const int b = (int)fdiv((uint32_t)tile, tl.dv_per);
-    const int rem = tile - b * per;
-    const int tt = (int)fdiv((uint32_t)rem, tl.dv_ntij), rem2 = rem - tt * ntij;
-    const int ti = (int)fdiv((uint32_t)rem2, tl.dv_ntj), tj = rem2 - ti * tl.ntJ;
-    const int t0 = tt * tl.BT, i0 = ti * tl.BI, j0 = tj * tl.BJ;
-    *stage_origin = (long long)b * g.S + (long long)t0 * g.P + (long long)i0 * g.Wp + j0;
-    const int bij = tl.BI * tl.BJ;
-    const int a = (int)fdiv((uint32_t)r, tl.dv_bij), ra = r - a * bij;
-    const int c = (int)fdiv((uint32_t)ra, tl.dv_bj), e = ra - c * tl.BJ;
-    const int t = t0 + a, i = i0 + c, j = j0 + e;
-    const bool ok = (r < tl.BT * bij) && t < g.T && i < g.H && j < g.H;
-    *lds_base = ok ? (a * (tl.BI + 2 * g.pad) + c) * (tl.BJ + 2 * g.pad) + e : 0;
+    const CellTile ct = cell_tile(tl, tile);
+    int a0, c0, e0, a, c, e;
+    cell_voxel(tl, ct.run * kTileRows, &a0, &c0, &e0);
+    *stage_origin = (long long)ct.b * g.S + (long long)a0 * g.P + (long long)(ct.i0 + c0) * g.Wp + ct.j0 + e0;
+    cell_voxel(tl, ct.run * kTileRows + r, &a, &c, &e);
+    const int i = ct.i0 + c, j = ct.j0 + e;
+    const bool ok = a < g.T && i < g.H && j < g.H;
+    *lds_base = ok ? (a - a0) * tl.sa + (c - c0) * tl.sb + e - e0 : 0;
     if (col) *col = ok ? j : -1;
     if (!ok) return false;
-    *pidx = padded_index(g, b, t, i, j);
+    *pidx = padded_index(g, ct.b, a, i, j);
     return true;
   }
 }
@@ -82,52 +105,13 @@ __host__ __device__ inline bool tile_row_coords(const Geom& g, const Tiling& tl,
     *j = s - *i * g.H;
     return true;
   }
-  const int per = tl.ntT * tl.ntI * tl.ntJ, ntij = tl.ntI * tl.ntJ;
-  *b = (int)fdiv((uint32_t)tile, tl.dv_per);
-  const int rem = tile - *b * per;
-  const int tt = (int)fdiv((uint32_t)rem, tl.dv_ntij), rem2 = rem - tt * ntij;
-  const int ti = (int)fdiv((uint32_t)rem2, tl.dv_ntj), tj = rem2 - ti * tl.ntJ;
-  const int bij = tl.BI * tl.BJ;
-  const int a = (int)fdiv((uint32_t)r, tl.dv_bij), ra = r - a * bij;
-  const int c = (int)fdiv((uint32_t)ra, tl.dv_bj), e = ra - c * tl.BJ;
-  *t = tt * tl.BT + a;
-  *i = ti * tl.BI + c;
-  *j = tj * tl.BJ + e;
-  return r < tl.BT * bij && *t < g.T && *i < g.H && *j < g.H;
-}
-
-// Padded (t, i, j) of a box-mode tile's staging origin.
-struct BoxOrigin {
-  int t0, i0, j0;
-};
-
-__host__ __device__ inline BoxOrigin box_origin(const Geom& g, const Tiling& tl, long long origin) {
-  BoxOrigin bo{0, 0, 0};
-  if (tl.mode == 1) {
-    const long long rem = origin % g.S;
-    bo.t0 = (int)(rem / g.P);
-    const int r2 = (int)(rem - (long long)bo.t0 * g.P);
-    bo.i0 = r2 / g.Wp;
-    bo.j0 = r2 - bo.i0 * g.Wp;
-  }
-  return bo;
-}
-
-// Global padded voxel of staged voxel vv (clamped to voxel 0, a zero halo
-// voxel, when outside the batch or outside the sample's padded box).
-__host__ __device__ inline long long staged_voxel(const Geom& g, const Tiling& tl, long long origin,
-                                                  const BoxOrigin& bo, int vv, long long limit) {
-  if (tl.mode == 0) {
-    const long long p = line_to_padded(g, origin + vv);
-    return (p < limit) ? p : 0;
-  }
-  const int bj2 = tl.BJ + 2 * g.pad, bij2 = (tl.BI + 2 * g.pad) * bj2;
-  const int a = vv / bij2;
-  const int rem = vv - a * bij2;
-  const int c = rem / bj2;
-  const int e = rem - c * bj2;
-  if (bo.t0 + a >= g.T + 2 * g.pad || bo.i0 + c >= g.Wp || bo.j0 + e >= g.Wp) return 0;
-  return origin + (long long)a * g.P + (long long)c * g.Wp + e;
+  const CellTile ct = cell_tile(tl, tile);
+  int c, e;
+  cell_voxel(tl, ct.run * kTileRows + r, t, &c, &e);
+  *b = ct.b;
+  *i = ct.i0 + c;
+  *j = ct.j0 + e;
+  return *t < g.T && *i < g.H && *j < g.H;
 }
 
 // Tile handled by persistent workgroup `wg` at iteration `it`: the 8 XCDs
@@ -143,28 +127,31 @@ __host__ __device__ inline int tile_of(int wg, int nwg, int it, int ntiles) {
   return t < ntiles ? t : -1;
 }
 
-// Staging source of a tile: its staging origin (see tile_row) and box origin.
+// Staging source of a tile: the origin (see tile_row), and in mode 1 the
+// line index of staged voxel 0 in the cell's padded line space, the cell's
+// first row and column, and what to add to a line's decoded a P + c Wp + e to
+// count from the origin.
 struct StageSrc {
   long long origin;
-  BoxOrigin bo;
+  int line0, i0, j0, back;
 };
 
-// The staging source of tile `tile` (mode 1: the box origin in padded
-// coordinates is the tile's first interior voxel, (t0, i0, j0) = (tt BT,
-// ti BI, tj BJ), shifted by the halo).
 __host__ __device__ inline StageSrc tile_source(const Geom& g, const Tiling& tl, int tile, int batch) {
-  StageSrc src;
-  long long p;
-  int lb;
-  tile_row(g, tl, tile, 0, batch, &p, &lb, &src.origin);
-  src.bo = BoxOrigin{0, 0, 0};
-  if (tl.mode == 1) {
-    const int per = tl.ntT * tl.ntI * tl.ntJ, ntij = tl.ntI * tl.ntJ;
-    const int b = (int)fdiv((uint32_t)tile, tl.dv_per);
-    const int rem = tile - b * per;
-    const int tt = (int)fdiv((uint32_t)rem, tl.dv_ntij), rem2 = rem - tt * ntij;
-    const int ti = (int)fdiv((uint32_t)rem2, tl.dv_ntj), tj = rem2 - ti * tl.ntJ;
-    src.bo = BoxOrigin{tt * tl.BT, ti * tl.BI, tj * tl.BJ};
+  StageSrc src{0, 0, 0, 0, 0};
+  if (tl.mode == 0) {
+    long long p;
+    int lb;
+    tile_row(g, tl, tile, 0, batch, &p, &lb, &src.origin);
+  } else {
+    const CellTile ct = cell_tile(tl, tile);
+    int a0, c0, e0;
+    cell_voxel(tl, ct.run * kTileRows, &a0, &c0, &e0);
+    const int first = a0 * g.P + c0 * g.Wp + e0;
+    src.origin = (long long)ct.b * g.S + first + (long long)ct.i0 * g.Wp + ct.j0;
+    src.line0 = a0 * tl.sa + c0 * tl.sb + e0;
+    src.i0 = ct.i0;
+    src.j0 = ct.j0;
+    src.back = -first;
   }
   return src;
 }
@@ -172,8 +159,8 @@ __host__ __device__ inline StageSrc tile_source(const Geom& g, const Tiling& tl,
 // Global padded voxel of staged voxel vv; -1 when it is outside the batch or
 // the sample's padded box (such voxels only feed rows that are discarded).
 template <int MODE>
-__host__ __device__ inline long long staged_voxel_fast(const Geom& g, const Tiling& tl, const StageSrc& src,
-                                                       int vv, long long limit) {
+__host__ __device__ inline long long staged_voxel(const Geom& g, const Tiling& tl, const StageSrc& src, int vv,
+                                                  long long limit) {
   if constexpr (MODE == 0) {
     const uint32_t u = (uint32_t)(src.origin + vv);  // < 2^31 (host check)
     const uint32_t tp = fastdiv(u, tl.div_a);
@@ -183,12 +170,13 @@ __host__ __device__ inline long long staged_voxel_fast(const Geom& g, const Tili
     const long long p = (long long)tp * g.P + (long long)ip * g.Wp + jj + 1;
     return p < limit ? p : -1;
   } else {
-  const int a = (int)fastdiv((uint32_t)vv, tl.div_a);
-  const int rem = vv - a * tl.sa;
-  const int c = (int)fastdiv((uint32_t)rem, tl.div_b);
-  const int e = rem - c * tl.sb;
-  if (src.bo.t0 + a >= g.T + 2 * g.pad || src.bo.i0 + c >= g.Wp || src.bo.j0 + e >= g.Wp) return -1;
-  return src.origin + (long long)a * g.P + (long long)c * g.Wp + e;
+    const int u = src.line0 + vv;
+    const int a = (int)fastdiv((uint32_t)u, tl.div_a);
+    const int rem = u - a * tl.sa;
+    const int c = (int)fastdiv((uint32_t)rem, tl.div_b);
+    const int e = rem - c * tl.sb;
+    if (a >= g.T + 2 * g.pad || src.i0 + c >= g.Wp || src.j0 + e >= g.Wp) return -1;
+    return src.origin + (a * g.P + c * g.Wp + e + src.back);
   }
 }
 
