@@ -77,8 +77,8 @@
  * and the activation are fp32, logits are fp32.  PD_DTYPE_FP32: fp32 end to
  * end.  flip = (logit > 0); a logit of exactly 0 is no flip.  Results are
  * bit-reproducible for a given handle and batch size; small batches split the
- * conv K loops over several workgroups, so two batch sizes can differ in the
- * fp32 summation order, and through an activation rounded to the other bf16
+ * conv K loops over the waves of a workgroup, so two batch sizes can differ in
+ * the fp32 summation order, and through an activation rounded to the other bf16
  * neighbour, by up to a few 1e-3 in the logits.
  * PD_DTYPE_FP8 (the paper deploys its models in FP8, Sec. VI, without
  * stating the scaling; this is the library's reading): OCP E4M3 values (4
@@ -192,7 +192,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
  *           the last layer at every grid site (channel order as in `flips`;
  *           H = d + 1 on the plaquette layout, d on the paper layout).
  * 1 <= batch <= max_batch.  Asynchronous on hip_stream.  The run works in the
- * handle's workspace (activations, parked sums, the hidden kernel's unit
+ * handle's workspace (activations, the hidden kernel's unit
  * counters): runs of one handle must not overlap (one stream, or the caller
  * orders them); separate handles are independent. */
 pd_status predecoder_run(pd_predecoder* h, void* hip_stream, const uint64_t* det, int32_t batch,
@@ -284,8 +284,8 @@ void predecoder_graph_destroy(pd_graph* g); /* NULL is a no-op; waits for the de
  * code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  predecoder_run_static takes the arguments of predecoder_run
  * and runs the same kernels, but keeps the workspace -- input planes,
- * activation buffers, projection outputs of residual networks, flip nibbles
- * and the parked sums of split K loops -- in a static device array of
+ * activation buffers, projection outputs of residual networks and flip
+ * nibbles -- in a static device array of
  * PD_STATIC_SCRATCH_BYTES bytes that the library holds on every device it
  * runs on until the process ends, instead of the handle's own workspace.  It
  * calls no allocating routine (the handle is made beforehand with
@@ -296,13 +296,9 @@ void predecoder_graph_destroy(pd_graph* g); /* NULL is a no-op; waits for the de
  *   buffers of batch S cmax a (cmax the widest activation row; a = 4 fp32, 2
  *   bf16, 1 fp8), for residual networks batch S pmax 2 (the widest projection),
  *   and batch V (flip nibbles) must fit, else PD_ERR_TOO_LARGE before any
- *   device work.  What is left holds the parked sums of small batches' split K
- *   loops (128 KiB per unit, up to the handle's one per compute unit); with
- *   fewer units a layer may split less than predecoder_run splits it, and the
- *   results then differ by the fp32 summation order, as two batch sizes can.
- *   With room for all units the results are bit-identical to predecoder_run's.
- *   (Batch 1 with 128 channels on the plaquette grid needs about 2 MB before
- *   the parked sums at d = 13 and 20 MB at d = 31.)
+ *   device work.  The results are bit-identical to predecoder_run's.
+ *   (Batch 1 with 128 channels on the plaquette grid needs about 2 MB at d = 13
+ *   and 20 MB at d = 31.)
  * Every call on one device uses that device's one array, which keeps the last
  * call's contents: each call clears what must start at zero (with a fill
  * kernel on hip_stream, no memset), and calls that overlap on one device --

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/predecoder.h"
+#include "conv_small.h"
 #include "internal.h"
 
 using pd::Geom;
@@ -28,8 +29,7 @@ constexpr size_t kSchedWords = 256;  // the hidden kernel's unit counters: 8 XCD
 
 // Device memory one run works in besides its inputs, outputs, weights and
 // tables: the input planes, the activation buffers, the projection outputs of
-// residual blocks, the flip nibbles, the parked sums of split K loops and the
-// hidden kernel's unit counters.
+// residual blocks, the flip nibbles and the hidden kernel's unit counters.
 // A handle owns one (sized for max_batch at create); predecoder_run_static
 // lays one over the library's static scratch array for each call.
 struct Workspace {
@@ -37,8 +37,6 @@ struct Workspace {
   void* act[3] = {nullptr, nullptr, nullptr};  // activations [batch * S][cmax]; act[2]: residual networks only
   void* pbuf = nullptr;                        // projection outputs [batch * S][pmax] (residual networks)
   uint8_t* nib = nullptr;                      // [batch][T][H][H] flip nibbles
-  float* partial = nullptr;                    // split K loops of small batches: fp32 sums of up to max_units units
-  long long max_units = 0;
   uint32_t* sched = nullptr;                   // the hidden kernel's unit counters (kSchedWords, zero between launches)
   size_t act_bytes = 0;                        // size of each activation buffer
   // Row width (bytes per voxel) of the data each activation buffer holds, 0
@@ -59,18 +57,13 @@ struct pd_predecoder {
   std::vector<pd_layer> layers;
   int ks = 3;                    // kernel size of the conv layers: 3, or 5 (Model 3 of Table models)
   Tiling tiling{};               // shared by every k x k x k layer (bf16 and fp8 paths)
+  Tiling small[2]{};             // tiles of 64 and 128 voxels for the small-launch kernel (span 0: none)
   Workspace ws;                  // sized for max_batch
   int32_t* tables = nullptr;
   std::vector<void*> wdev;       // per conv layer: fragments
   std::vector<size_t> wslice;    // per conv layer: bytes of the fragments of one 128-channel slice of a
                                  // 256-wide layer (run as two slices), 0 otherwise
   std::vector<float*> bdev;      // per conv layer: bias fp32 (a 3x3x3 output layer: [4] biases, [4] scales)
-  // per conv layer of 64 to 256 input and output channels run by the hidden
-  // kernel (else null): its fragments and biases (fp8: and scales) as slices
-  // of 32 output channels, and (128 or 256 output channels) as slices of 64,
-  // for small batches (more workgroups per layer)
-  std::vector<void*> wnarrow, whalf;
-  std::vector<float*> bnarrow, bhalf;
   float* head_w = nullptr;       // [4][c_in] fp32 (bf16-valued on the bf16 path)
   float* head_b = nullptr;       // [4]
   // residual network (predecoder_create_resnet): its blocks; wdev / wslice /
@@ -238,30 +231,67 @@ long long flat_span(const Geom& g, long long seg_len, long long nseg, int batch)
   return best;
 }
 
-// The most lines a tile of a cell of n voxels stages (cell line space, see
-// pd::Tiling); limit + 1 when over `limit`.  Tiles repeat their place in the
-// cell's rounds after at most BI BJ of them.
-int cell_span(const Tiling& t, int n, int pad, int limit) {
+// The most lines a tile (`rows` voxels) of a cell of n voxels stages (cell
+// line space, see pd::Tiling); limit + 1 when over `limit`.  Tiles repeat
+// their place in the cell's rounds after at most BI BJ of them.
+int cell_span(const Tiling& t, int n, int pad, int rows, int limit) {
   const int bij = t.BI * t.BJ;
   const int halo = 2 * pad * (t.sa + t.sb + 1) + 1;
-  if (n >= pd::kTileRows && halo + pd::kTileRows - 1 > limit) return limit + 1;  // most cells: no need to look closer
+  if (n >= rows && halo + rows - 1 > limit) return limit + 1;  // most cells: no need to look closer
   auto line = [&](int u) {
     const int r = u % bij;
     return u / bij * t.sa + r / t.BJ * t.sb + r % t.BJ;
   };
   int best = 0;
   for (int k = 0; k < std::min(t.ntT, bij) && best <= limit; ++k) {
-    const int u0 = k * pd::kTileRows, u1 = std::min(u0 + pd::kTileRows, n) - 1;
+    const int u0 = k * rows, u1 = std::min(u0 + rows, n) - 1;
     best = std::max(best, line(u1) - line(u0) + halo);
   }
   return std::min(best, limit + 1);
+}
+
+// The tiling by cells of BI x BJ with tiles of `rows` voxels; span limit + 1
+// when a tile stages more than `limit` lines.
+Tiling cell_tiling(const Geom& g, int BI, int BJ, int rows, int limit) {
+  const int p = g.pad;
+  Tiling t{};
+  t.mode = 1;
+  t.BI = BI;
+  t.BJ = BJ;
+  t.ntT = (g.T * BI * BJ + rows - 1) / rows;
+  t.ntI = (g.H + BI - 1) / BI;
+  t.ntJ = (g.H + BJ - 1) / BJ;
+  t.sa = (BI + 2 * p) * (BJ + 2 * p);
+  t.sb = BJ + 2 * p;
+  t.span = cell_span(t, g.T * BI * BJ, p, rows, limit);
+  return t;
+}
+
+// Tiling of the small-launch kernel (span 0 where no cell fits): the fewest
+// tiles of `rows` voxels, weighed against what a tile stages (500 lines cost
+// as much as a quarter more tiles) and the LDS bank conflicts of very short
+// cell rows.
+Tiling plan_small(const Geom& g, int rows, int ks) {
+  const int limit = pd::conv_small_span(ks);
+  Tiling best{};
+  double least = 0.0;
+  for (int BJ = 1; BJ <= g.H; ++BJ)
+    for (int BI = 1; BI <= g.H; ++BI) {
+      const Tiling t = cell_tiling(g, BI, BJ, rows, limit);
+      if (t.span > limit) continue;
+      const double cost = (double)t.ntT * t.ntI * t.ntJ * (1.0 + 0.0005 * t.span) * (BJ < 4 ? 1.08 : 1.0);
+      if (best.span == 0 || cost < least) {
+        best = t;
+        least = cost;
+      }
+    }
+  return best;
 }
 
 Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
   // 5x5x5 layers: their own (larger) staging buffers, cells on a halo of two
   const int kMaxSpan = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                : pd::conv_hidden_max_span(5);
-  const int p = g.pad;
   Tiling best{};
   long long best_rows = -1;
   int best_span = 0;
@@ -275,7 +305,7 @@ Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
     }
   };
   // flat, tiles inside one sample (a halo of one only)
-  if (p == 1) {
+  if (g.pad == 1) {
     Tiling t{};
     t.mode = 0;
     t.seg_len = g.V;
@@ -286,7 +316,7 @@ Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
     consider(t, 2ll * t.tiles_per_seg * pd::kTileRows);
   }
   // flat across samples (rows per sample ~ V); the span bound covers any batch
-  if (max_batch > 1 && p == 1) {
+  if (max_batch > 1 && g.pad == 1) {
     Tiling t{};
     t.mode = 0;
     t.seg_len = -1;  // set per run to batch * V
@@ -300,16 +330,7 @@ Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
   // cells
   for (int BJ = 1; BJ <= g.H; ++BJ)
     for (int BI = 1; BI <= g.H; ++BI) {
-      Tiling t{};
-      t.mode = 1;
-      t.BI = BI;
-      t.BJ = BJ;
-      t.ntT = (g.T * BI * BJ + pd::kTileRows - 1) / pd::kTileRows;
-      t.ntI = (g.H + BI - 1) / BI;
-      t.ntJ = (g.H + BJ - 1) / BJ;
-      t.sa = (BI + 2 * p) * (BJ + 2 * p);
-      t.sb = BJ + 2 * p;
-      t.span = cell_span(t, g.T * BI * BJ, p, kMaxSpan);
+      const Tiling t = cell_tiling(g, BI, BJ, pd::kTileRows, kMaxSpan);
       // (a cell row of BJ < 16 voxels, whose 16-lane LDS reads span two
       // staged lines, costs little: at d = T = 25 a 5x3x16 box and a 9x13x2
       // box reached 0.54 and 0.53 of peak per MFMA row, so the row count
@@ -498,13 +519,8 @@ void free_all(pd_predecoder* h) {
   f(h->tables);
   for (void* p : h->wdev) f(p);
   for (float* p : h->bdev) f(p);
-  for (void* p : h->wnarrow) f(p);
-  for (float* p : h->bnarrow) f(p);
-  for (void* p : h->whalf) f(p);
-  for (float* p : h->bhalf) f(p);
   f(h->head_w);
   f(h->head_b);
-  f(h->ws.partial);
   f(h->ws.sched);
   h->ws.planes = h->ws.act[0] = h->ws.act[1] = nullptr;
   h->ws.nib = nullptr;
@@ -512,12 +528,7 @@ void free_all(pd_predecoder* h) {
   h->wdev.clear();
   h->wslice.clear();
   h->bdev.clear();
-  h->wnarrow.clear();
-  h->bnarrow.clear();
-  h->whalf.clear();
-  h->bhalf.clear();
   h->head_w = h->head_b = nullptr;
-  h->ws.partial = nullptr;
   h->ws.sched = nullptr;
 }
 
@@ -651,106 +662,257 @@ struct StopAt {
   int row_bytes = 0;
 };
 
-// Split of a layer's K loop over 2^k workgroups per tile.  Only small
-// batches split (tiles x parts within the workspace's units, one per compute
-// unit for a handle's own: past that the parked fp32 sums cost more than the
-// shorter loops gain); parts must divide the layer's input-channel chunks.
-// Among the splits that fit, the one with the least estimated time of a
-// workgroup's unit: its chunks, then either the tile's epilogue (bias,
-// activation and stores, done by the tile's single workgroup) or parking the
-// fp32 sums plus the second, elementwise kernel that finishes all tiles in
-// parallel.  Microseconds per unit on MI355X at batch 1, from per-phase
-// timestamps inside the kernel: a 16-channel chunk 2.5 (64 output channels)
-// or 3.9 (128); the activation epilogue 3.3 or 7.3; parking 1.75 or 3.4;
-// the finishing kernel with its launch about 8.  (For 64 channels at 25^3
-// one unsplit launch beats two parts by 3 us; for 128 channels at 13^3 the
-// split saves 20 us.)  fp8 chunks are 32 channels with about half a bf16
-// chunk's matrix time per channel; a 5x5x5 chunk has 125 taps instead of 27.
-// nsl: the layer's output-channel slices of cout channels, all in the one
-// launch (each is a unit of its own per tile and part).  unit_us (optional):
-// the estimate for an unsplit unit.
-pd::Split_k split_for(const Workspace& ws, const Tiling& t, int cin, int cout, int fp8, int ks = 3, int nsl = 1,
-                      double* unit_us = nullptr) {
-  const int kch = pd::conv_hidden_chunk_channels(fp8);
-  const int nch = cin / kch;
-  const double wide = cout > 64 ? 1.0 : 0.0;
-  const double chunk = (2.5 + 1.4 * wide) * (fp8 ? 1.1 : 1.0) * (ks * ks * ks) / 27.0;
-  const double epi = 3.3 + 4.0 * wide, park = 1.75 + 1.65 * wide;
-  const double finish = 8.0;
-  pd::Split_k sk{0, ws.partial, ws.max_units};
-  sk.sched = ws.sched;
-  while ((1 << sk.lsl) < nsl) ++sk.lsl;
-  double best = nch * chunk + epi;
+// A hidden layer's call: c_out channels in slices of cw (weights and biases
+// per slice), epi as in launch_conv_hidden (2: the 5x5x5 output layer).
+// carries_head: the layer before a 1x1x1 head, whether or not this run
+// applies it (epi 1) -- a run that stops at it must sum as the head's run does.
+struct LayerRun {
+  int cin, cout, cw, act;
+  const void* x;
+  void* y;
+  const void* wfrag;
+  const float* bias;
+  int epi = 0;
+  const float *head_w = nullptr, *head_b = nullptr;
+  bool carries_head = false;
+  const uint16_t* sc = nullptr;
+  int sc_stride = 0;
+};
+
+// ---- The K parts of a layer's sums (bf16).  A sum is taken as P = 2^k parts
+// of consecutive input-channel chunks, added in order.  P depends on the
+// layer and the launch's size only, never on the kernel that runs it, so a
+// handle's results for a batch size do not depend on how its launches are
+// shaped: few tiles (a small batch) take more parts, whose chains run side
+// by side, up to one unit (tile, output slice, part) per compute unit.  Of
+// the counts that fit, the least estimate in microseconds of a unit's time:
+// its 16-channel chunks (2.5 each for 32 or 64 output channels, 3.9 for 128;
+// a 5x5x5 chunk has 125 taps instead of 27) and its epilogue, or a part's
+// share of the chunks and what parting costs.
+int split_parts(const pd_predecoder* h, long long tiles, int cin, int width, int nsl, double* unit_us = nullptr) {
+  const bool fp8 = h->dtype == PD_DTYPE_FP8;  // 32-channel chunks
+  const int nch = cin / (fp8 ? 32 : 16);
+  const double wide = width > 64 ? 1.0 : 0.0;
+  const double chunk = (2.5 + 1.4 * wide) * (fp8 ? 1.1 : 1.0) * (h->ks * h->ks * h->ks) / 27.0;
+  double best = nch * chunk + 3.3 + 4.0 * wide;
   if (unit_us) *unit_us = best;
-  for (int k = 1; nch % (1 << k) == 0 && (t.ntiles << (k + sk.lsl)) <= ws.max_units; ++k) {
-    const double est = (nch >> k) * chunk + park + finish;
+  int parts = 1;
+  for (int k = 1; nch % (1 << k) == 0 && ((tiles * nsl) << k) <= h->n_cu; ++k) {
+    const double est = (nch >> k) * chunk + 1.75 + 1.65 * wide + 8.0;
     if (est < best) {
       best = est;
-      sk.kshift = k;
+      parts = 1 << k;
     }
   }
-  return sk;
+  return parts;
 }
 
-// One hidden-kernel layer over the batch (nsl output-channel slices of cw
-// channels; see launch_conv_hidden for the rest).  Usually one launch.  When
-// the layer's units (tiles x slices) fill the workgroup slots a few times
-// over and leave a short remainder, two: the first samples, whose units fill
-// whole rounds, unsplit; then the last few samples (a sub-batch: every
-// per-sample pointer moved on by their offset) with their K loops split over
-// the otherwise idle chip and finished by the second kernel.  A remainder of
-// r units would otherwise take a whole unit's time on r slots (40 of 552
-// units at Model 6's 13^3 batch 16 took about a third of the layer); the
-// split saves that time but one fraction 2^-k, and costs the parked sums,
-// the finishing kernel and one more kernel boundary: about 45 us in all,
-// from MI355X timings of splits of 128 to 512 input channels (Models 1, 2
-// and 6 at 13^3), so only long units split.  (Model 6 at 13^3 batch 16 in
-// bf16: the last 2 of the 16 samples split in two, 5 % less time per round.)
+// ... counted over slices of 32 or 64 output channels where those still fit
+// the compute units (for the layer before a head only if it parts as a whole).
+int conv_parts(const pd_predecoder* h, const LayerRun& L, long long tiles) {
+  const int C = h->n_cu;
+  if (h->blocks.empty() && h->ks == 3 && L.cin <= 128) {
+    const bool sliced = !L.carries_head || split_parts(h, tiles, L.cin, L.cout, 1) > 1;
+    if (sliced && tiles * (L.cout / 32) <= C) return split_parts(h, tiles, L.cin, 32, L.cout / 32);
+    if (sliced && L.cout >= 128 && tiles * (L.cout / 64) <= C) return split_parts(h, tiles, L.cin, 64, L.cout / 64);
+  }
+  return split_parts(h, tiles, L.cin, L.cw, L.cout / L.cw);
+}
+
+// ---- Which kernel runs a hidden layer: the persistent one (launch_conv_hidden:
+// 256-voxel tiles, two workgroups per CU; sums of one part) or the one for
+// small launches (launch_conv_small).  Both times are estimated in
+// microseconds and the smaller one wins.  The estimates follow MI355X
+// measurements per layer of 64-, 128- and 256-wide networks from d = 5 to 31
+// at batches 1 to 8 to about 15 %; at the line the two are as close
+// (small / persistent, 128 channels: bf16 45 / 48 us at 41k voxels, 76 / 78 at
+// 81k, 100 / 94 at 127k; fp8 42 / 50 at 81k, 62 / 56 at 127k; at 32k voxels
+// 27 / 48, fp8 19 / 32).
+
+// Small launches: a workgroup costs `fixed` (start, staging, the sums'
+// exchange, epilogue) and `piece` per 128-byte piece of its input rows.  Where
+// two fit a CU, a further one costs less than the first.  kg: K groups, which
+// the parts fill up to four (fp8: always four).
+struct SmallShape {
+  int kg, rows, cols, acc;  // acc: accumulator registers of a lane
+  double fixed, piece;
+};
+constexpr SmallShape kSmallBf16[] = {
+    {1, 64, 64, 16, 4.5, 3.7},  {1, 128, 64, 32, 4.3, 7.3}, {1, 128, 128, 64, 6.0, 9.5},
+    {2, 64, 32, 16, 3.9, 2.7},  {2, 64, 64, 32, 4.0, 5.0},  {2, 128, 64, 64, 4.5, 5.0},
+    {4, 64, 32, 32, 3.9, 1.65}, {4, 64, 64, 64, 3.6, 2.7},  {4, 128, 32, 64, 4.0, 3.0}};
+constexpr SmallShape kSmallFp8[] = {{4, 64, 32, 32, 4.5, 1.35}, {4, 64, 64, 64, 4.4, 2.35}, {4, 128, 64, 128, 5.4, 4.4}};
+constexpr SmallShape kSmall5[] = {
+    {1, 64, 64, 16, 5.0, 14.5}, {1, 128, 64, 32, 5.0, 26.3}, {1, 128, 128, 64, 6.0, 43.0},
+    {2, 64, 32, 16, 4.5, 9.7},  {2, 64, 64, 32, 5.0, 18.0},  {2, 128, 64, 64, 5.0, 22.0},
+    {4, 64, 32, 32, 4.5, 9.7},  {4, 64, 64, 64, 5.0, 17.0},  {4, 128, 32, 64, 5.0, 13.5}};
+
+double small_us(const pd_predecoder* h, const LayerRun& L, int batch, int parts, pd::SmallPlan* plan) {
+  const bool fp8 = h->dtype == PD_DTYPE_FP8;
+  const int row = L.cin * (fp8 ? 1 : 2), kg = fp8 ? 4 : std::min(parts, 4);
+  const int cout = L.epi == 2 ? 32 : L.cout;
+  double best = 1e30;
+  auto consider = [&](const SmallShape& s) {
+    const Tiling& t = h->small[s.rows == 128];
+    if (s.kg != kg || t.span == 0 || L.cw % s.cols != 0 || (parts > 4 && !fp8 && s.rows != 64)) return;
+    // (a fused head needs all channels in the tile; wider ones take a kernel of their own)
+    if (L.carries_head && cout == 64 && s.cols != 64) return;
+    const long long units = (long long)batch * t.ntT * t.ntI * t.ntJ * (cout / s.cols);
+    const int per_cu = pd::conv_small_occupancy(h->ks, row <= 128, s.acc);
+    const long long rounds = (units + (long long)h->n_cu * per_cu - 1) / ((long long)h->n_cu * per_cu);
+    const long long turns = (units + h->n_cu - 1) / h->n_cu;  // workgroups a CU runs
+    const double pieces = row < 128 ? 0.8 : row / 128.0;
+    const double us = per_cu == 1 ? rounds * (s.fixed + s.piece * pieces)
+                                  : s.fixed * (1.0 + 0.75 * (rounds - 1)) +
+                                        s.piece * pieces * (turns == 1 ? 1.0 : 0.82 * turns);
+    if (us < best) {
+      best = us;
+      *plan = {s.rows, s.cols, parts};
+    }
+  };
+  if (h->ks == 5)
+    for (const SmallShape& s : kSmall5) consider(s);
+  else if (fp8)
+    for (const SmallShape& s : kSmallFp8) consider(s);
+  else
+    for (const SmallShape& s : kSmallBf16) consider(s);
+  return best + (L.carries_head && L.cout != 64 ? 4.0 : 0.0);
+}
+
+// The persistent kernel: t1 for units of one workgroup per CU or fewer, t2 for
+// a full round of two per CU, from a unit's matrix time m at 2.1 GHz.
+struct BigTime {
+  double t1, t2;
+  long long round;  // units of a full round
+};
+
+BigTime big_time(const pd_predecoder* h, const LayerRun& L) {
+  const bool fp8 = h->dtype == PD_DTYPE_FP8;
+  const int taps = h->ks * h->ks * h->ks;
+  const double steps = fp8 ? L.cin / 32 * ((taps + 1) / 2) * 2.0 : L.cin / 16 * taps;
+  const double m = steps * (L.cw / 16) * 32 / 2100.0;
+  if (h->ks == 5) return {1.4 * m, 1.4 * m, h->n_cu};
+  if (fp8) return {1.7 * m + 8.0, 3.6 * m + 7.0, 2ll * h->n_cu};
+  return {1.75 * m + (L.cw == 64 ? 8.0 : 3.0), 3.3 * m + 12.0, 2ll * h->n_cu};
+}
+
+double big_us(const BigTime& b, long long units) {
+  const long long q = units / b.round, r = units % b.round;
+  const double half = b.round / 2.0;
+  const double rest = r == 0 ? 0.0 : (r <= half ? b.t1 : b.t1 + (b.t2 - b.t1) * (0.5 + 0.5 * (r - half) / half));
+  return q * b.t2 + rest;
+}
+
+// Launches of samples b0 .. b0 + nb - 1 (every per-sample pointer moved on).
+pd::HiddenCall layer_call(const pd_predecoder* h, Workspace& ws, const Tiling& t, const LayerRun& L, float* logits,
+                          int b0, int nb, hipStream_t st) {
+  const Geom& g = h->g;
+  const int esz = h->dtype == PD_DTYPE_FP8 ? 1 : 2;  // bytes per activation value
+  const long long pv = (long long)b0 * g.S;          // padded voxels before sample b0
+  pd::HiddenCall c{};
+  c.g = &g;
+  c.tl = &t;
+  c.cin = L.cin;
+  c.cout = L.cout;
+  c.act = L.act;
+  c.x = (const char*)L.x + pv * L.cin * esz;
+  c.y = L.y ? (char*)L.y + pv * L.cout * esz : nullptr;
+  c.ystride = L.cout;
+  c.wfrag = L.wfrag;
+  c.bias = L.bias;
+  c.epi = L.epi;
+  c.head_w = L.head_w;
+  c.head_b = L.head_b;
+  c.tables = h->tables;
+  c.nib = ws.nib + (long long)b0 * g.V;
+  c.logits = logits ? logits + (long long)b0 * 4 * g.T * g.H * g.H : nullptr;
+  c.batch = nb;
+  c.n_workgroups = h->n_cu * pd::conv_hidden_workgroups_per_cu(h->ks);
+  c.sched = ws.sched;
+  c.sc = !L.sc ? nullptr : (const uint16_t*)((const char*)L.sc + pv * L.sc_stride * (L.head_w ? 2 : esz));
+  c.sc_stride = L.sc_stride;
+  c.ks = h->ks;
+  c.slice_width = L.cw;
+  c.stream = st;
+  return c;
+}
+
+pd_status run_small(const pd_predecoder* h, Workspace& ws, const LayerRun& L, const pd::SmallPlan& plan, float* logits,
+                    int b0, int nb, hipStream_t st) {
+  const bool fp8 = h->dtype == PD_DTYPE_FP8;
+  Tiling t = h->small[plan.rows == 128];
+  tiling_for_batch(&t, h->g, nb);
+  pd::HiddenCall c = layer_call(h, ws, t, L, logits, b0, nb, st);
+  const bool head_after = L.epi == 1 && L.cout != 64;
+  if (head_after) c.epi = 0;
+  pd_status s = check_launch(pd::launch_conv_small(plan, c, fp8));
+  if (s == PD_OK && head_after)
+    s = check_launch(pd::launch_head(h->g, L.cout, c.y, fp8, L.head_w, L.head_b, h->tables, c.nib, c.logits, nb, st));
+  return s;
+}
+
+pd_status run_big(const pd_predecoder* h, Workspace& ws, const LayerRun& L, float* logits, int nb, hipStream_t st) {
+  Tiling t = h->tiling;
+  tiling_for_batch(&t, h->g, nb);
+  pd::HiddenCall c = layer_call(h, ws, t, L, logits, 0, nb, st);
+  c.cout = L.cw;
+  while ((L.cw << c.lsl) < L.cout) ++c.lsl;
+  return check_launch(pd::launch_conv_hidden(c, h->dtype == PD_DTYPE_FP8));
+}
+
+// One hidden layer over the batch.  When its units fill the persistent
+// kernel's slots one to four times over and leave a short remainder, which
+// would take a whole unit's time with most of the chip idle, the first
+// samples, whose units fill whole rounds, run there and the last few, with
+// their sums in parts, on the small-launch kernel -- for long units only
+// (512 input channels in bf16): the second launch and the shorter batch's
+// parts cost about 45 us.  (Model 6 at 13^3, batch 16: 552 units on 512
+// slots, the last 2 samples.)
 constexpr long long kMaxTailRounds = 4;  // past this, a remainder costs little
 constexpr double kTailCostUs = 45.0;
 
-pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const Tiling& tl, int cin, int cw, int nsl, int act,
-                     const void* x, void* y, int ystride, const void* wfrag, const float* bias, int head,
-                     const float* head_w, const float* head_b, float* logits, int batch, int fp8,
-                     const uint16_t* sc, int sc_stride, int ks, hipStream_t st) {
-  const Geom& g = h->g;
-  const int slots = h->n_cu * pd::conv_hidden_workgroups_per_cu(ks);
-  // samples b0 .. b0 + nb - 1 with tiling t and split sk
-  auto launch = [&](const Tiling& t, const pd::Split_k& sk, int b0, int nb) {
-    const int esz = fp8 ? 1 : 2;                  // bytes per activation value
-    const long long pv = (long long)b0 * g.S;     // padded voxels before sample b0
-    const uint16_t* scb = !sc ? nullptr
-                              : (const uint16_t*)((const char*)sc + pv * sc_stride * (head_w ? 2 : esz));
-    return check_launch(pd::launch_conv_hidden(
-        g, t, cin, cw, act, (const char*)x + pv * cin * esz, y ? (char*)y + pv * ystride * esz : nullptr, ystride,
-        wfrag, bias, head, head_w, head_b, h->tables, ws.nib + (long long)b0 * g.V,
-        logits ? logits + (long long)b0 * 4 * g.T * g.H * g.H : nullptr, nb, slots, sk, fp8, scb, sc_stride, ks,
-        st));
+pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, float* logits, int batch,
+                     hipStream_t st) {
+  pd::SmallPlan plan{};
+  if (L.epi == 2) {  // the 5x5x5 output layer: 4 filters on one block of 32
+    (void)small_us(h, L, batch, 4, &plan);
+    return run_small(h, ws, L, plan, logits, 0, batch, st);
+  }
+  const int nsl = L.cout / L.cw;
+  const BigTime bt = big_time(h, L);
+  auto tiles_of = [&](int nb) {
+    Tiling t = h->tiling;
+    tiling_for_batch(&t, h->g, nb);
+    return t.ntiles;
   };
-  const pd::Split_k sk = split_for(ws, tl, cin, cw, fp8, ks, nsl);
-  const long long units = tl.ntiles * nsl, q = units / slots, r = units % slots;
-  if (sk.kshift == 0 && q >= 1 && q <= kMaxTailRounds && r > 0 && batch > 1) {
+  // samples b0 .. b0 + nb - 1 with sums of `parts` parts
+  auto run = [&](int b0, int nb, int parts) {
+    const double small = small_us(h, L, nb, parts, &plan);
+    if (parts > 1 || small * 1.05 < big_us(bt, tiles_of(nb) * nsl)) return run_small(h, ws, L, plan, logits, b0, nb, st);
+    return run_big(h, ws, L, logits, nb, st);
+  };
+  const long long tiles = tiles_of(batch), units = tiles * nsl, q = units / bt.round;
+  const bool fp8 = h->dtype == PD_DTYPE_FP8;
+  const int parts = fp8 ? 1 : conv_parts(h, L, tiles);
+  if (parts == 1 && q >= 1 && q <= kMaxTailRounds && units % bt.round != 0) {
     // the most first samples whose tiles fit q full rounds (tiles grow with
     // the batch: per sample, or one flat run of batch x V voxels)
     const Tiling& base = h->tiling;
-    const long long fit = q * slots / nsl;  // tiles
+    const long long fit = q * bt.round / nsl;  // tiles
     const bool flat = base.mode == 0 && (base.seg_len < 0 || base.tiles_per_seg == 0);
     const long long per = base.mode == 1 ? (long long)base.ntT * base.ntI * base.ntJ : base.tiles_per_seg;
-    const long long first = flat ? fit * pd::kTileRows / g.V : fit / per;
+    const long long first = flat ? fit * pd::kTileRows / h->g.V : fit / per;
     if (first >= 1 && first < batch) {
       const int nb = batch - (int)first;
-      Tiling th = base, tt = base;
-      tiling_for_batch(&th, g, (int)first);
-      tiling_for_batch(&tt, g, nb);
       double unit_us = 0.0;
-      const pd::Split_k tsk = split_for(ws, tt, cin, cw, fp8, ks, nsl, &unit_us);
-      if (tsk.kshift > 0 && unit_us * (1.0 - 1.0 / (1 << tsk.kshift)) > kTailCostUs) {
-        const pd_status s = launch(th, sk, 0, batch - nb);
-        return s != PD_OK ? s : launch(tt, tsk, batch - nb, nb);
+      const int tail_parts = split_parts(h, tiles_of(nb), L.cin, L.cw, nsl, &unit_us);
+      if (tail_parts > 1 && unit_us * (1.0 - 1.0 / tail_parts) > kTailCostUs) {
+        const pd_status s = run(0, (int)first, 1);
+        return s != PD_OK ? s : run((int)first, nb, tail_parts);
       }
     }
   }
-  return launch(tl, sk, 0, batch);
+  return run(0, batch, parts);
 }
 
 // The path of a residual network (Model 6, Sec. VI, Fig. Model8Representation):
@@ -775,8 +937,6 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
   pd_status s;
   if ((s = mark()) != PD_OK) return s;
   if ((s = check_launch(pd::launch_unpack(g, h->tables, det, batch, ws.planes, 1, 0, st))) != PD_OK) return s;
-  Tiling tl = h->tiling;
-  tiling_for_batch(&tl, g, batch);
   const void* x = ws.planes;
   int xi = -1;     // index of x in ws.act (-1: the planes)
   int conv = 0;    // convs run so far (the numbering of `stop`)
@@ -810,8 +970,8 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
                                                  batch, fp8, 3, st));
         }
       } else {
-        s = run_hidden(h, ws, tl, B.c_in, cw, nsl, B.act, x, hb, B.c_mid, h->wdev[2 * k], h->bdev[2 * k], 0, nullptr,
-                       nullptr, nullptr, batch, fp8, nullptr, 0, 3, st);
+        LayerRun L{B.c_in, B.c_mid, cw, B.act, x, hb, h->wdev[2 * k], h->bdev[2 * k]};
+        s = run_hidden(h, ws, L, nullptr, batch, st);
       }
       if (s != PD_OK) return s;
       if (stopped(hb, B.c_mid * ae)) return PD_OK;
@@ -851,9 +1011,11 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
                                            ws.nib, logits, batch, h->n_cu, fp8, sc, sc_stride, nullptr, nullptr,
                                            nullptr, st));
     } else {  // slices as for conv1, each also with its shortcut channels (or projection rows)
-      const int nsl = B.c_out > 128 ? B.c_out / 128 : 1, cw = B.c_out / nsl;
-      s = run_hidden(h, ws, tl, B.c_mid, cw, nsl, B.act, hb, yb, B.c_out, h->wdev[2 * k + 1], h->bdev[2 * k + 1], 4,
-                     pw, pb, nullptr, batch, fp8, sc, sc_stride, 3, st);
+      LayerRun L{B.c_mid, B.c_out, std::min(B.c_out, 128), B.act, hb, yb, h->wdev[2 * k + 1], h->bdev[2 * k + 1], 4,
+                 pw, pb};
+      L.sc = sc;
+      L.sc_stride = sc_stride;
+      s = run_hidden(h, ws, L, nullptr, batch, st);
     }
     if (s != PD_OK) return s;
     if (!last && stopped(yb, B.c_out * ae)) return PD_OK;
@@ -927,34 +1089,10 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
           s = check_launch(pd::launch_conv_first(g, L.c_in, cw, L.act, x, yk, L.c_out, wk, h->bdev[l] + k * cw,
                                                  batch, fp8, ks, st));
         }
-      } else if (l < (int)h->wnarrow.size() && h->wnarrow[l] && tl.ntiles * (L.c_out / 32) <= h->n_cu &&
-                 (!head_layer || (L.c_in <= 128 && (tl.ntiles * (L.c_out / 32)) <= ws.max_units &&
-                                  split_for(ws, tl, L.c_in, L.c_out, fp8, ks).kshift > 0))) {
-        // a small batch: a 64- to 256-wide layer as 32-channel slices, two to
-        // eight times the workgroups (still at most one per CU) for the same
-        // staging, in place of splitting its K loops (a 256-channel input's
-        // long loops may still split).  The layer that carries the head, when
-        // unsliced it would split its K loops and finish in a second kernel
-        // anyway: its slices park their sums and that kernel finishes whole
-        // rows with the head (d = 13, batch 1, 8 x 128: 2.6 % less time per
-        // round in bf16, 4 % in fp8; a head layer that runs whole in one
-        // launch stays so, the extra kernel costing more: 3 % at d = 25,
-        // 6 x 64).  A run that stops at it slices it the same way, so that
-        // its exported activations are the ones the head reads.
-        s = run_hidden(h, ws, tl, L.c_in, 32, L.c_out / 32, L.act, x, y, L.c_out, h->wnarrow[l], h->bnarrow[l],
-                       fuse_head ? 1 : 0, fuse_head ? h->head_w : nullptr, fuse_head ? h->head_b : nullptr, logits,
-                       batch, fp8, nullptr, 0, ks, st);
-      } else if (l < (int)h->whalf.size() && h->whalf[l] && tl.ntiles * (L.c_out / 64) <= h->n_cu &&
-                 (!head_layer || (L.c_in <= 128 && (tl.ntiles * (L.c_out / 64)) <= ws.max_units &&
-                                  split_for(ws, tl, L.c_in, L.c_out, fp8, ks).kshift > 0))) {
-        // ... or, with too many tiles for that, a 128- or 256-wide one as
-        // slices of 64 (the head layer as above)
-        s = run_hidden(h, ws, tl, L.c_in, 64, L.c_out / 64, L.act, x, y, L.c_out, h->whalf[l], h->bhalf[l],
-                       fuse_head ? 1 : 0, fuse_head ? h->head_w : nullptr, fuse_head ? h->head_b : nullptr, logits,
-                       batch, fp8, nullptr, 0, ks, st);
       } else {  // the last hidden layer may carry the head and the threshold in its epilogue
-        s = run_hidden(h, ws, tl, L.c_in, cw, nsl, L.act, x, y, L.c_out, h->wdev[l], h->bdev[l], fuse_head ? 1 : 0,
-                       h->head_w, h->head_b, logits, batch, fp8, nullptr, 0, ks, st);
+        LayerRun R{L.c_in, L.c_out, cw, L.act, x, y, h->wdev[l], h->bdev[l], fuse_head ? 1 : 0, h->head_w, h->head_b,
+                   head_layer};
+        s = run_hidden(h, ws, R, logits, batch, st);
       }
       head_done = fuse_head && l > 0;
     }
@@ -975,10 +1113,10 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
                                          batch, h->n_cu, fp8, nullptr, 0, nullptr, nullptr, nullptr, st));
   } else if (out3) {
     const pd_layer& L = h->layers[n - 1];
-    s = run_hidden(h, ws, tl, L.c_in, L.c_out, 1, L.act, x, nullptr, 0, h->wdev[n - 1], h->bdev[n - 1], 2, nullptr,
-                   nullptr, logits, batch, fp8, nullptr, 0, ks, st);
+    LayerRun R{L.c_in, L.c_out, 32, L.act, x, nullptr, h->wdev[n - 1], h->bdev[n - 1], 2};
+    s = run_hidden(h, ws, R, logits, batch, st);
   } else if (!head_done) {  // a one-hidden-layer network on the paper's layout
-    s = check_launch(pd::launch_head(g, h->layers[n - 1].c_in, x, h->head_w, h->head_b, h->tables, ws.nib, logits,
+    s = check_launch(pd::launch_head(g, h->layers[n - 1].c_in, x, 0, h->head_w, h->head_b, h->tables, ws.nib, logits,
                                      batch, st));
   }
   if (s != PD_OK) return s;
@@ -1099,6 +1237,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
   h->cmax = cmax;
   if (dtype != PD_DTYPE_FP32) {
     h->tiling = plan_tiling(g, max_batch, ks);
+    for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, ks);
     const int max_span = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                  : pd::conv_hidden_max_span(5);
     if (h->tiling.span <= 0 || h->tiling.span > max_span) {
@@ -1124,11 +1263,6 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
   if ((s = dev_alloc(&h->ws.act[1], vox * cmax * aelem)) != PD_OK) return fail(s);
   if ((s = dev_alloc(&h->ws.nib, (size_t)max_batch * g.V)) != PD_OK) return fail(s);
   if (dtype != PD_DTYPE_FP32) {
-    // parked fp32 sums of split K loops: room for one unit per compute unit
-    h->ws.max_units = h->n_cu;
-    if ((s = dev_alloc(&h->ws.partial, (size_t)h->ws.max_units * pd::conv_hidden_partial_floats_per_unit() * 4)) !=
-        PD_OK)
-      return fail(s);
     if ((s = dev_alloc(&h->ws.sched, kSchedWords * 4)) != PD_OK) return fail(s);
     if (hipMemset(h->ws.sched, 0, kSchedWords * 4) != hipSuccess) return fail(PD_ERR_DEVICE);
   }
@@ -1247,43 +1381,6 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
     s = upload(&bd, bias_dev.data(), bias_dev.size() * 4);
     h->bdev.push_back(bd);
     if (s != PD_OK) return fail(s);
-    // a 64- or 128-wide layer of the hidden kernel: also as slices of sw
-    // output channels (fragments back to back; per slice its biases, then
-    // (fp8) its scales)
-    auto slices = [&](int sw, void** wn, float** bn) -> pd_status {
-      std::vector<float> bq;
-      pd_status st;
-      if (dtype == PD_DTYPE_FP8) {
-        std::vector<uint8_t> f;
-        for (int q = 0; q < L.c_out / sw; ++q) {
-          std::vector<uint8_t> fq = conv_fragments_fp8(codes.data() + (size_t)sw * q * L.c_in * 27, L.c_in, sw);
-          f.insert(f.end(), fq.begin(), fq.end());
-          bq.insert(bq.end(), b + sw * q, b + sw * (q + 1));
-          bq.insert(bq.end(), scale.begin() + sw * q, scale.begin() + sw * (q + 1));
-        }
-        st = upload(wn, f.data(), f.size());
-      } else {
-        std::vector<uint16_t> f;
-        for (int q = 0; q < L.c_out / sw; ++q) {
-          std::vector<uint16_t> fq = conv_fragments(w + (size_t)sw * q * L.c_in * 27, L.c_in, sw);
-          f.insert(f.end(), fq.begin(), fq.end());
-        }
-        st = upload(wn, f.data(), f.size() * 2);
-        bq.assign(b, b + L.c_out);
-      }
-      return st != PD_OK ? st : upload(bn, bq.data(), bq.size() * 4);
-    };
-    for (auto* v : {&h->wnarrow, &h->whalf}) v->resize(h->wdev.size(), nullptr);
-    for (auto* v : {&h->bnarrow, &h->bhalf}) v->resize(h->wdev.size(), nullptr);
-    // (256 input channels: 32-channel slices in fp8 only, no 64-channel
-    // ones -- in bf16 their 16-chunk K loops measured slower than the split
-    // loops of 128-channel slices, at batch 1 of Models 2 and 5)
-    auto width_ok = [](int c) { return c == 64 || c == 128 || c == 256; };
-    if (i > 0 && L.k == 3 && width_ok(L.c_in) && width_ok(L.c_out) && dtype != PD_DTYPE_FP32) {
-      if (L.c_in <= 128 || dtype == PD_DTYPE_FP8) s = slices(32, &h->wnarrow.back(), &h->bnarrow.back());
-      if (s == PD_OK && L.c_in <= 128 && L.c_out >= 128) s = slices(64, &h->whalf.back(), &h->bhalf.back());
-    }
-    if (s != PD_OK) return fail(s);
   }
   if (hipDeviceSynchronize() != hipSuccess) return fail(PD_ERR_DEVICE);
   *out = h;
@@ -1377,6 +1474,7 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
     return PD_ERR_DEVICE;
   }
   h->tiling = plan_tiling(g, max_batch);
+  for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, 3);
   if (h->tiling.span <= 0 || h->tiling.span > pd::conv_hidden_max_span(3)) {
     delete h;
     return PD_ERR_UNSUPPORTED;
@@ -1403,9 +1501,6 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
   if ((s = dev_alloc(&h->ws.act[2], vox * cmax * 2)) != PD_OK) return fail(s);
   if ((s = dev_alloc(&h->ws.pbuf, vox * pmax * 2)) != PD_OK) return fail(s);
   if ((s = dev_alloc(&h->ws.nib, (size_t)max_batch * g.V)) != PD_OK) return fail(s);
-  h->ws.max_units = h->n_cu;
-  if ((s = dev_alloc(&h->ws.partial, (size_t)h->ws.max_units * pd::conv_hidden_partial_floats_per_unit() * 4)) != PD_OK)
-    return fail(s);
   if ((s = dev_alloc(&h->ws.sched, kSchedWords * 4)) != PD_OK) return fail(s);
   if (hipMemset(h->ws.sched, 0, kSchedWords * 4) != hipSuccess) return fail(PD_ERR_DEVICE);
   std::vector<int32_t> tab = build_tables(g);
@@ -1553,7 +1648,7 @@ pd_status run_in_region(pd_predecoder* h, hipStream_t st, const uint64_t* det, i
   const size_t cin0 = resnet ? (size_t)h->blocks[0].c_in : (size_t)h->layers[0].c_in;
   const size_t vox = (size_t)batch * (size_t)g.S;
   // regions of 256-byte aligned offsets: planes, activations, projection
-  // outputs (residual networks), flip nibbles, then the parked sums
+  // outputs (residual networks), flip nibbles
   size_t off = 0;
   auto carve = [&](size_t n) {
     const size_t at = (off + 255) & ~(size_t)255;
@@ -1578,13 +1673,6 @@ pd_status run_in_region(pd_predecoder* h, hipStream_t st, const uint64_t* det, i
   ws.pbuf = resnet ? (void*)(b + o_pbuf) : nullptr;
   ws.nib = (uint8_t*)(b + o_nib);
   ws.act_bytes = act_bytes;
-  if (!fp32) {  // what is left holds the parked sums of up to the handle's own number of units
-    const size_t unit = pd::conv_hidden_partial_floats_per_unit() * 4;
-    const size_t o_part = carve(0);
-    const long long fit = (long long)((bytes - std::min(bytes, o_part)) / unit);
-    ws.max_units = std::min(h->ws.max_units, fit);
-    ws.partial = (float*)(b + o_part);
-  }
   // the zero halos the 3x3x3 layers read: the planes and every activation
   // buffer start all zero (a fill kernel, so that the call can be captured
   // into a graph); the other regions are written before they are read

@@ -10,8 +10,6 @@ hipError_t launch_hidden_head<false>(const HiddenCall& c) {
   PD_HIDDEN_CASE(128, 128, EPI_HEAD)
   PD_HIDDEN_CASE(64, 128, EPI_HEAD)
   PD_HIDDEN_CASE(128, 64, EPI_HEAD)
-  PD_HIDDEN_CASE(64, 32, EPI_HEAD)  // the head layer in 32-channel slices (small batches)
-  PD_HIDDEN_CASE(128, 32, EPI_HEAD)
   return hipErrorInvalidValue;
 }
 

@@ -52,6 +52,7 @@
 
 #include "activation.h"
 #include "conv_hidden.h"
+#include "shortcut.h"
 #include "tiles.h"
 
 namespace pd {
@@ -139,26 +140,23 @@ __host__ __device__ inline int stage_slot(int q) {
   return (v < BV - 1 ? v : BV - 1) * VSTRIDE + stage_gran(q) * 16;
 }
 
-// Epilogue modes: the activations of a hidden layer, a hidden layer with the
-// 1x1x1 head fused in, or the 5x5x5 output layer itself (4 filters, padded to
-// one block of 32 MFMA rows; the 3x3x3 one has a kernel of its own); EPI_PARK: one part of a split K loop, whose
-// fp32 sums are parked for split_finish_kernel.  Only EPI_PARK kernels split
-// (the others see a split of 1 at compile time and keep their registers for
-// the epilogue).  EPI_ADD: EPI_ACT with the block's shortcut added to the
-// pre-activation (the second conv of a residual block): the bf16 row of sc
-// at the output voxel (fp8: E4M3 codes), or, when head_w is given, its 1x1x1
-// projection computed here from the sc_stride (<= 8) channels of sc's row
-// (head_w [c_out][sc_stride] and head_b [c_out] in those slots:
+// Epilogue modes: the activations of a hidden layer, or a hidden layer with
+// the 1x1x1 head fused in (2, the output layer of 5x5x5 networks, runs on the
+// small-launch kernel).  EPI_ADD: EPI_ACT with the block's shortcut added to
+// the pre-activation (the second conv of a residual block): the bf16 row of
+// sc at the output voxel (fp8: E4M3 codes), or, when head_w is given, its
+// 1x1x1 projection computed here from the sc_stride (<= 8) channels of sc's
+// row (head_w [c_out][sc_stride] and head_b [c_out] in those slots:
 // bf16(head_b + sum_ci head_w x_ci), an fp32 FMA chain in channel order;
 // fp8: E4M3 of the same).
-enum Epi { EPI_ACT = 0, EPI_HEAD = 1, EPI_OUT = 2, EPI_PARK = 3, EPI_ADD = 4 };
+enum Epi { EPI_ACT = 0, EPI_HEAD = 1, EPI_ADD = 4 };
 
 // Wave split of the 256 x COUT output tile: WN waves across the channels
-// (NB blocks of 32 each: 2, or 1 for the 32-row output layer), WM across the
-// voxels (ROWS each, MB blocks of 32).
+// (NB = 2 blocks of 32 each), WM across the voxels (ROWS each, MB blocks of
+// 32).
 template <int COUT>
 struct Split {
-  static constexpr int NB = COUT >= 64 ? 2 : 1;
+  static constexpr int NB = 2;
   static constexpr int WN = COUT / (32 * NB);
   static constexpr int WM = (NT / 64) / WN;
   static constexpr int ROWS = kTileRows / WM;
@@ -173,20 +171,19 @@ struct Split {
 // per-channel weight scales [COUT] (fp8) and the head weights [4][COUT].
 // The head epilogue puts its partial sums in the staging buffer the tile
 // read last.
-// output-channel slices of one launch: up to 8 of 32 channels (a 256-wide
-// layer), else up to 4
-__host__ __device__ constexpr int max_slices(int cout) { return cout == 32 ? 8 : 4; }
+// output-channel slices of one launch: up to 4
+constexpr int kMaxSlices = 4;
 
 template <int COUT, int KS>
 struct Lds {
   static constexpr int ABUF = Conv<KS>::ABUF;
   static constexpr int zero = 2 * ABUF;
-  // biases (fp8: then the weight scales) of up to max_slices(COUT)
+  // biases (fp8: then the weight scales) of up to kMaxSlices
   // output-channel slices; a head's weights (never sliced) follow one slice's
   static constexpr int bias = zero + 512;
   static constexpr int headw = bias + 2 * COUT * 4;
   // two unit numbers handed between the waves (dynamic scheduling)
-  static constexpr int sched = bias + (2 * max_slices(COUT) > 6 ? 2 * max_slices(COUT) : 6) * COUT * 4;
+  static constexpr int sched = bias + 2 * kMaxSlices * COUT * 4;
   static constexpr int total = sched + 16;
   static_assert(zero % 256 == 0, "zero region must be 256-aligned");
   static_assert(Conv<KS>::WG_PER_CU * total <= 160 * 1024, "the workgroups of a CU fit its LDS");
@@ -240,67 +237,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t stage_rsrc(const void* x, long
   return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)x + base * ROW + cb), 0, kStageRange, 0x00020000);
 }
 
-// The projected shortcut of channels co .. co + N - 1 at padded voxel p:
-// b[c] + sum_ci w[c][ci] x[p][ci] over the pc channels of x's row (the
-// network's input planes, bf16 on both paths), an fp32 FMA chain in channel
-// order, rounded to bf16 (F8: to E4M3).
-template <int N, bool F8>
-__device__ __forceinline__ void project_shortcut(const uint16_t* __restrict__ x, int pc, long long p,
-                                                 const float* __restrict__ w, const float* __restrict__ b, int co,
-                                                 float (&s)[N]) {
-  float a[N];
-#pragma unroll
-  for (int o = 0; o < N; ++o) a[o] = b[co + o];
-  for (int ci = 0; ci < pc; ++ci) {
-    const float xv = __uint_as_float((uint32_t)x[p * pc + ci] << 16);
-#pragma unroll
-    for (int o = 0; o < N; ++o) a[o] = __builtin_fmaf(w[(co + o) * pc + ci], xv, a[o]);
-  }
-#pragma unroll
-  for (int o = 0; o < N; o += 2) {
-    if constexpr (F8) {
-      s[o] = e4m3_round(a[o]);
-      s[o + 1] = e4m3_round(a[o + 1]);
-    } else {
-      const uint32_t pk = bf16_pack(a[o], a[o + 1]);
-      s[o] = __uint_as_float(pk << 16);
-      s[o + 1] = __uint_as_float(pk & 0xFFFF0000u);
-    }
-  }
-}
-
-// The block's shortcut of channels co .. co + N - 1 at padded voxel p: its
-// stored row in sc (bf16, or F8 E4M3 codes), or with w given its
-// projection from sc's few channels (the input planes).
-template <int N, bool F8>
-__device__ __forceinline__ void shortcut_of(const uint16_t* __restrict__ sc, int sc_stride, long long p,
-                                            const float* __restrict__ w, const float* __restrict__ b, int co,
-                                            float (&s)[N]) {
-  if (w) {
-    project_shortcut<N, F8>(sc, sc_stride, p, w, b, co, s);
-  } else if constexpr (F8) {
-    const uint8_t* r = (const uint8_t*)sc + p * sc_stride + co;
-#pragma unroll
-    for (int o = 0; o < N; o += 4) {
-      const uint32_t q = *reinterpret_cast<const uint32_t*>(r + o);
-      s[o] = __builtin_amdgcn_cvt_f32_fp8((int)q, 0);
-      s[o + 1] = __builtin_amdgcn_cvt_f32_fp8((int)q, 1);
-      s[o + 2] = __builtin_amdgcn_cvt_f32_fp8((int)q, 2);
-      s[o + 3] = __builtin_amdgcn_cvt_f32_fp8((int)q, 3);
-    }
-  } else {
-    const uint16_t* r = sc + p * sc_stride + co;
-#pragma unroll
-    for (int o = 0; o < N; o += 4) {
-      const u32x2 q = *reinterpret_cast<const u32x2*>(r + o);
-      s[o] = __uint_as_float(q.x << 16);
-      s[o + 1] = __uint_as_float(q.x & 0xFFFF0000u);
-      s[o + 2] = __uint_as_float(q.y << 16);
-      s[o + 3] = __uint_as_float(q.y & 0xFFFF0000u);
-    }
-  }
-}
-
 // F8: E4M3 activations and weights (bias holds [COUT] biases then [COUT]
 // per-channel weight scales; y and x hold one byte per value).  KS: the
 // kernel size, 3 or 5 (5: cells on a halo of two).
@@ -311,8 +247,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
                    int ystride, const u32x4* __restrict__ wfrag, const float* __restrict__ bias,
                    const float* __restrict__ head_w, const float* __restrict__ head_b,
                    const int32_t* __restrict__ tables, uint8_t* __restrict__ nib,
-                   float* __restrict__ logits, int batch, int kshift_arg, float* __restrict__ partial,
-                   const uint16_t* __restrict__ sc, int sc_stride, int lsl, uint32_t* __restrict__ sched,
+                   float* __restrict__ logits, int batch, const uint16_t* __restrict__ sc, int sc_stride, int lsl, uint32_t* __restrict__ sched,
                    int nstat) {
   static_assert(KS == 3 || MODE == 1, "5x5x5 layers run on cell tiles");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -323,10 +258,9 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   constexpr int NBT = COUT / 32;  // 32-channel blocks in total
   using P = Prec<F8, KS>;
   constexpr int KCH = P::KCH, NSTEP = P::NSTEP, SG = P::SG;
-  // weight ring depth: 32-channel slices (small batches, one workgroup per
-  // CU, two MFMAs per k-step) prefetch a third of a chunk ahead, since the
-  // short steps alone cannot cover a load's latency
-  constexpr int RING = (COUT == 32 && KS == 3) ? (F8 ? 7 : 9) : P::RING;
+  // weight ring depth: a 64-wide bf16 layer has registers for eight steps
+  // ahead (7 % less time where a CU holds one workgroup: d = 31, batch 1)
+  constexpr int RING = KS == 3 && COUT == 64 && !F8 ? 9 : P::RING;
   static_assert(NSTEP % RING == 0, "the weight ring lines up with chunk boundaries");
   constexpr int RMAX = Conv<KS>::RMAX, ABUF = L::ABUF, TAPS = Conv<KS>::TAPS;
   constexpr int ROW = CIN * P::ESZ;  // bytes per input voxel row
@@ -338,21 +272,14 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   const uint32_t hmask = half ? 0xFFFFFFFFu : 0u;  // fp8: selects the half-wave's tap
   const int ntiles = (int)tl.ntiles;
   const long long limit = (long long)batch * g.S;
-  // Work units: (tile, part); part p of a tile runs its chunks [p NCU, (p+1) NCU)
-  // with ksplit = 2^kshift parts per tile (EPI_PARK only: small batches).
-  // With parts, each unit parks its fp32 sums in `partial` (unit u at
-  // u * 256 * COUT floats) and split_finish_kernel does the epilogue.
-  const int kshift = EPI == EPI_PARK ? kshift_arg : 0;
-  const int ksplit = 1 << kshift;
-  const int NCU = NCHUNK >> kshift;  // chunks per unit
-  // Output-channel slices (a layer wider than COUT in one launch): 2^lsl
-  // slices of COUT channels, unit u = ((tile << lsl | slice) << kshift) | part;
-  // slice q has its own weight fragments (the layer's TSTEPS k-steps, after
-  // q slices' worth), biases (COUT, fp8: and COUT scales) and output
-  // columns (and shortcut columns, or projection rows).
-  const int nunits = ntiles << (kshift + lsl);
+  // Work units: (tile, slice).  Output-channel slices (a layer wider than
+  // COUT in one launch): 2^lsl slices of COUT channels, unit u = tile << lsl
+  // | slice; slice q has its own weight fragments (the layer's TSTEPS
+  // k-steps, after q slices' worth), biases (COUT, fp8: and COUT scales) and
+  // output columns (and shortcut columns, or projection rows).
+  const int nunits = ntiles << lsl;
   constexpr int BSL = (F8 ? 2 : 1) * COUT;  // bias floats per slice
-  auto slice_of = [&](int u) { return (u >> kshift) & ((1 << lsl) - 1); };
+  auto slice_of = [&](int u) { return u & ((1 << lsl) - 1); };
 
   lds_char* const lds = (lds_char*)smem;
   lds_char* const zero = lds + L::zero;
@@ -386,36 +313,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
 
       // ---- epilogue: lane holds channels co .. co + 3 (co = 64 wn + 32 nb +
       // 8 q + 4 half) of voxel row wm ROWS + 32 mb + l32 ----
-      if constexpr (EPI == EPI_OUT) {
-        // the output layer: rows 0..3 of the channel block are the four logits
-        // (+ bias, no activation), held by the lanes of the first half-wave
-        if (half == 0) {
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb) {
-            int b, t, i, j;
-            if (tile_row_coords(g, tl, tile, wm * W::ROWS + mb * 32 + l32, batch, &b, &t, &i, &j)) {
-              float lg[4];
-#pragma unroll
-              for (int o = 0; o < 4; ++o)
-                lg[o] = F8 ? __builtin_fmaf(acc[mb][0][o], scale_s[o], bias_s[o]) : acc[mb][0][o] + bias_s[o];
-              if (sc) {  // residual shortcut of the last block: 4 bf16 channels
-                const u32x2 sv = *reinterpret_cast<const u32x2*>(sc + padded_index(g, b, t, i, j) * sc_stride);
-                lg[0] += __uint_as_float(sv.x << 16);
-                lg[1] += __uint_as_float(sv.x & 0xFFFF0000u);
-                lg[2] += __uint_as_float(sv.y << 16);
-                lg[3] += __uint_as_float(sv.y & 0xFFFF0000u);
-              }
-              const int HH = g.H * g.H;
-              const int s = i * g.H + j;
-              nib[(long long)b * g.V + (long long)t * HH + s] = (uint8_t)flip_nibble(g, tables, i, j, lg);
-              if (logits) {
-#pragma unroll
-                for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + s] = lg[o];
-              }
-            }
-          }
-        }
-      } else if constexpr (EPI == EPI_ACT || EPI == EPI_ADD) {
+      if constexpr (EPI == EPI_ACT || EPI == EPI_ADD) {
         // bias + activation + bf16, transposed through this wave's slice of
         // the staging buffer the tile read last (64 rows x 128 bytes, granule
         // c of row r at c ^ (r % 8)), then stored as the wave's whole part of
@@ -623,7 +521,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
     finish_sched();
     return;
   }
-  int tile = unit >> (kshift + lsl);
+  int tile = unit >> lsl;
 
   auto source_of = [&](int t) { return tile_source(g, tl, t, batch); };
   long long cur_base = stage_base<MODE>(g, source_of(tile));
@@ -641,39 +539,15 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   const uint32_t wbytes = (uint32_t)(TSTEPS * NBT * P::WFRAG) << lsl;
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)wfrag, 0, wbytes, 0x00020000);
 
-  // Small-batch launches of 32-channel slices have one workgroup per CU or
-  // fewer, whose short k-steps would each wait on their weight fragments
-  // coming from memory one after the other.  First the XCD's workgroups warm
-  // its L2 with all the layer's fragments, each loading a share at once (up
-  // to 32 KB), alongside the first chunk's staging; the values are folded
-  // into one register, kept to the end of the prologue.  (fp8 at d = 25,
-  // batch 1: 8 % less time per round.  Split K loops, whose k-steps are
-  // four times as long, gained nothing from it.)
-  constexpr bool WARM = COUT == 32 && KS == 3;
-  uint32_t warm = 0;
-  if constexpr (WARM) {
-    const uint32_t per = (gridDim.x >> 3) > 0 ? (gridDim.x >> 3) : 1u;  // this XCD's workgroups
-    const uint32_t share = ((wbytes + per - 1) / per + NT * 16 - 1) / (NT * 16) * (NT * 16);
-    const uint32_t b0 = (blockIdx.x >> 3) * share;
-    u32x4 pf[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)  // offsets past the fragments read zeros
-      pf[i] = (uint32_t)i * NT * 16 < share ? __builtin_amdgcn_raw_buffer_load_b128(wres, b0 + (i * NT + tid) * 16, 0, 0)
-                                             : u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) warm ^= pf[i].x;
-  }
-
   // First tile: stage its first chunk synchronously.
   {
-    const __amdgpu_buffer_rsrc_t rs = stage_rsrc<ROW>(x, cur_base, (unit & (ksplit - 1)) * NCU * 32);
+    const __amdgpu_buffer_rsrc_t rs = stage_rsrc<ROW>(x, cur_base, 0);
 #pragma unroll
     for (int k = 0; k < RMAX; ++k) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, soff[k], 0, 0);
       *(lds_u32x4_w*)(lds + stage_slot<KS>(k * NT + tid)) = v;
     }
   }
-  if constexpr (WARM) asm volatile("" ::"v"(warm));
   const uint32_t woff = (uint32_t)((wn * NB * 64 + lane) * 16 * WQ);
   auto wload = [&](int gs, int nb, u32x4 (&dst)[WQ]) {
 #pragma unroll
@@ -687,12 +561,11 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   for (int st = 0; st < RING - 1; ++st)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
-      wload(slice_of(unit) * TSTEPS + (unit & (ksplit - 1)) * NCU * NSTEP + st, nb, bq[st][nb]);
+      wload(slice_of(unit) * TSTEPS + st, nb, bq[st][nb]);
   __syncthreads();  // staged chunk, bias, zero region and head weights visible
 
   int gchunk = 0;  // chunks processed by this workgroup (selects the LDS buffer)
   for (int it = 0; unit >= 0; ++it) {
-    const int c0 = (unit & (ksplit - 1)) * NCU;  // first chunk of this unit
     const int slice = slice_of(unit);
     int next_unit;
     if (!sched || it + 1 < nstat) {
@@ -705,8 +578,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
     uint32_t grabbed = 0;
     if (sched && tid == 0 && it + 2 >= nstat)
       grabbed = __hip_atomic_fetch_add(grab, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int next = next_unit >= 0 ? next_unit >> (kshift + lsl) : -1;
-    const int next_c0 = next_unit >= 0 ? (next_unit & (ksplit - 1)) * NCU : 0;
+    const int next = next_unit >= 0 ? next_unit >> lsl : -1;
     const int next_slice = next_unit >= 0 ? slice_of(next_unit) : 0;
     const StageSrc next_src = source_of(next >= 0 ? next : tile);
     const long long next_base = stage_base<MODE>(g, next_src);
@@ -734,18 +606,17 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
 
-    for (int chunk = 0; chunk < NCU; ++chunk, ++gchunk) {
+    for (int chunk = 0; chunk < NCHUNK; ++chunk, ++gchunk) {
       lds_char* const cur = lds + (gchunk & 1) * ABUF;
       lds_char* const oth = lds + ((gchunk + 1) & 1) * ABUF;
-      const int cc = c0 + chunk;  // the channel chunk this step loop reads
       // the chunk staged next: the following chunk of this unit, else the
       // first chunk of the next unit, else nothing
-      const bool more = chunk + 1 < NCU;
+      const bool more = chunk + 1 < NCHUNK;
       const int sspan = (more || next >= 0) ? tl.span : 0;  // staged voxels of the chunk staged next
       // the next tile's offsets replace soff round by round during the
       // last chunk (past the last tile: none, every granule empty)
       const __amdgpu_buffer_rsrc_t srs =
-          more ? stage_rsrc<ROW>(x, cur_base, (cc + 1) * 32) : stage_rsrc<ROW>(x, next_base, next_c0 * 32);
+          more ? stage_rsrc<ROW>(x, cur_base, (chunk + 1) * 32) : stage_rsrc<ROW>(x, next_base, 0);
       u32x4 stg;
 
       uint32_t rbase[MB];
@@ -825,15 +696,11 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
                                                          __builtin_bit_cast(bf16x8, a[0]), c, 0, 0, 0);
         }
       };
-      // One register set of activation fragments (two for 32-channel
-      // slices): av[mb] is re-read for the next step as soon as this step's
+      // One register set of activation fragments: av[mb] is re-read for the next step as soon as this step's
       // two MFMAs on it have issued, so it has the other row blocks' MFMAs to
       // arrive.  Weight fragments are loaded RING - 1 steps ahead, staging
       // rounds in the shadow of row block 0.
-      // AD: steps between a fragment's read and its use -- two for 32-channel
-      // slices, whose two MFMAs per step alone do not cover a read's latency
-      constexpr int AD = (COUT == 32 && KS == 3) ? 2 : 1;
-      u32x4 av[AD][MB][AQ];
+      u32x4 av[MB][AQ];
       // Wave priority: a SIMD runs one wave of each of the two workgroups on
       // the CU; the one in its K loop goes ahead of one in staging waits or
       // the epilogue (1), and a wave about to issue MFMAs ahead of both (2),
@@ -843,11 +710,9 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
       // gain in bf16).
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int d = 0; d < AD; ++d)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) frag_read(mb, d, av[d][mb]);
-      const int gbase = slice * TSTEPS + cc * NSTEP;                  // k-step of this chunk's step 0
-      const int nbase = next_slice * TSTEPS + next_c0 * NSTEP - NSTEP;  // ... of the next unit's first chunk, minus NSTEP
+      for (int mb = 0; mb < MB; ++mb) frag_read(mb, 0, av[mb]);
+      const int gbase = slice * TSTEPS + chunk * NSTEP;  // k-step of this chunk's step 0
+      const int nbase = next_slice * TSTEPS - NSTEP;     // ... of the next unit's first chunk, minus NSTEP
       // staging of the next chunk: round k is loaded at step SG k and stored
       // to LDS at step SG (k + 1), just before round k + 1 is loaded (a round
       // that would be stored past the last step is stored after it)
@@ -872,10 +737,10 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
         for (int mb = 0; mb < MB; ++mb) {
           __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(bq[st % RING][nb], av[st % AD][mb], acc[mb][nb]);
+          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(bq[st % RING][nb], av[mb], acc[mb][nb]);
           if constexpr (!F8) __builtin_amdgcn_s_setprio(1);
           __builtin_amdgcn_sched_barrier(0);
-          if (st + AD < NSTEP) frag_read(mb, st + AD, av[st % AD][mb]);
+          if (st + 1 < NSTEP) frag_read(mb, st + 1, av[mb]);
           if constexpr (F8) __builtin_amdgcn_s_setprio(1);  // fp8: the fragment reads go out at 2 too
           if (mb == 0) {
             if (st >= SG && st % SG == 0 && st / SG - 1 < RMAX) stage_store(st / SG - 1);
@@ -896,23 +761,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
       __builtin_amdgcn_s_barrier();
     }
 
-    if constexpr (EPI == EPI_PARK) {
-      // split K loop: park this unit's fp32 sums as [tile row][channel]; a
-      // second kernel adds a tile's parts and applies the epilogue
-      float* const mine = partial + (size_t)unit * kTileRows * COUT;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int row = wm * W::ROWS + mb * 32 + l32, co = (wn * NB + nb) * 32 + q * 8 + half * 4;
-            *reinterpret_cast<float4*>(mine + row * COUT + co) =
-                float4{acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]};
-          }
-    } else {
-      finish_tile(tile, slice, lds + ((gchunk - 1) & 1) * ABUF, acc);
-    }
+    finish_tile(tile, slice, lds + ((gchunk - 1) & 1) * ABUF, acc);
     unit = next_unit;
     tile = next;
     cur_base = next_base;
@@ -921,216 +770,25 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   finish_sched();
 }
 
-// Second kernel of a split K loop: one thread per (tile row, 8 channels)
-// (activations) or per tile row (head, output layer) adds the tile's parts
-// in part order, then applies the epilogue of the unsplit kernel: bias,
-// activation, bf16 and a 16-byte store; or bias, activation, bf16 rounding,
-// the 1x1x1 head and the threshold; or, for the output layer, bias and the
-// threshold.  F8: the sums are scaled by the channel's weight scale (bias
-// + cout) before the bias, and activations are stored as E4M3.
-template <int EPI, int ACT, bool F8>
-__global__ void __launch_bounds__(256) split_finish_kernel(Geom g, Tiling tl, int cout, int kshift,
-                                                           const float* __restrict__ partial,
-                                                           const float* __restrict__ bias, void* __restrict__ y,
-                                                           int ystride, const float* __restrict__ head_w,
-                                                           const float* __restrict__ head_b,
-                                                           const int32_t* __restrict__ tables,
-                                                           uint8_t* __restrict__ nib, float* __restrict__ logits,
-                                                           int batch, const uint16_t* __restrict__ sc, int sc_stride,
-                                                           int lsl) {
-  constexpr bool ROWS8 = EPI == EPI_ACT || EPI == EPI_ADD;  // one thread per (row, 8 channels)
-  // the head: one thread per (row, 8 channels) too, of every slice of the
-  // row (hsl: the slices a row's lanes span), the rows' partial head sums
-  // reduced over the row's consecutive lanes
-  const int hsl = EPI == EPI_HEAD ? lsl : 0, tsl = lsl - hsl;
-  const int groups = (ROWS8 || EPI == EPI_HEAD) ? (cout << hsl) / 8 : 1;
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= ((long long)tl.ntiles << tsl) * kTileRows * groups) return;
-  // (tile, output-channel slice) of this thread: activations only; the head
-  // and the output layer take whole rows
-  const int ts = (int)(gid / (kTileRows * groups));
-  const int tile = ts >> tsl, slice = ts & ((1 << tsl) - 1);
-  const int rem = (int)(gid - (long long)ts * kTileRows * groups);
-  const int r = rem / groups, grp = rem - r * groups;
-  const int ksplit = 1 << kshift;
-  if (tsl) {  // this slice's biases, outputs, and shortcut columns or projection rows
-    bias += (size_t)slice * (F8 ? 2 : 1) * cout;
-    y = (char*)y + (size_t)slice * cout * (F8 ? 1 : 2);
-    if (head_w) {
-      head_w += (size_t)slice * cout * sc_stride;
-      head_b += (size_t)slice * cout;
-    } else if (sc) {
-      sc = (const uint16_t*)((const char*)sc + (size_t)slice * cout * (F8 ? 1 : 2));
-    }
-  }
-  // pre-activation of channels c .. c + 7 of this row in the slice whose
-  // units are u << kshift .. (part p: + p) and biases bs: the sum over the
-  // tile's parts in part order (fp8: times the channel's weight scale), plus
-  // the bias
-  // Parts are added strictly in part order; from four parts on they are read
-  // four at a time, so the four reads go out together.
-  auto sum8 = [&](int u, const float* bs, int c, float (&v)[8]) {
-    if (ksplit < 4) {
-      for (int p = 0; p < ksplit; ++p) {
-        const float* src = partial + ((size_t)((u << kshift) + p) * kTileRows + r) * cout + c;
-        const float4 a = *reinterpret_cast<const float4*>(src);
-        const float4 b = *reinterpret_cast<const float4*>(src + 4);
-        const float t[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = p == 0 ? t[e] : v[e] + t[e];
-      }
-    }
-    for (int p0 = 0; p0 < ksplit && ksplit >= 4; p0 += 4) {
-      float4 a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int p = p0 + q;  // < ksplit: ksplit is a power of two >= 4
-        const float* src = partial + ((size_t)((u << kshift) + p) * kTileRows + r) * cout + c;
-        a[q] = *reinterpret_cast<const float4*>(src);
-        b[q] = *reinterpret_cast<const float4*>(src + 4);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int p = p0 + q;
-        const float t[8] = {a[q].x, a[q].y, a[q].z, a[q].w, b[q].x, b[q].y, b[q].z, b[q].w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = p == 0 ? t[e] : v[e] + t[e];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = F8 ? __builtin_fmaf(v[e], bs[cout + c + e], bs[c + e]) : v[e] + bs[c + e];
-  };
-  if constexpr (ROWS8) {
-    long long pidx, o;
-    int lb;
-    if (!tile_row(g, tl, tile, r, batch, &pidx, &lb, &o)) return;
-    float v[8];
-    sum8(ts, bias, grp * 8, v);
-    if constexpr (EPI == EPI_ADD) {  // the block's shortcut
-      float pj[8];
-      shortcut_of<8, F8>(sc, sc_stride, pidx, head_w, head_b, grp * 8, pj);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += pj[e];
-    }
-    if constexpr (F8) {
-      const uint32_t w0 = e4m3_pack4(act_fn<ACT>(v[0]), act_fn<ACT>(v[1]), act_fn<ACT>(v[2]), act_fn<ACT>(v[3]));
-      const uint32_t w1 = e4m3_pack4(act_fn<ACT>(v[4]), act_fn<ACT>(v[5]), act_fn<ACT>(v[6]), act_fn<ACT>(v[7]));
-      *reinterpret_cast<uint2*>((uint8_t*)y + pidx * ystride + grp * 8) = uint2{w0, w1};
-    } else {
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = bf16_pack(act_fn<ACT>(v[2 * e]), act_fn<ACT>(v[2 * e + 1]));
-      *reinterpret_cast<uint4*>((uint16_t*)y + pidx * ystride + grp * 8) = uint4{w[0], w[1], w[2], w[3]};
-    }
-  } else {
-    int b, t, i, j;
-    if (!tile_row_coords(g, tl, tile, r, batch, &b, &t, &i, &j)) return;
-    float lg[4];
-    if constexpr (EPI == EPI_OUT) {
-      float v[8];
-      sum8(ts, bias, 0, v);
-#pragma unroll
-      for (int o2 = 0; o2 < 4; ++o2) lg[o2] = v[o2];
-      if (sc) {  // residual shortcut of the last block
-        const uint2 sv = *reinterpret_cast<const uint2*>(sc + padded_index(g, b, t, i, j) * sc_stride);
-        lg[0] += __uint_as_float(sv.x << 16);
-        lg[1] += __uint_as_float(sv.x & 0xFFFF0000u);
-        lg[2] += __uint_as_float(sv.y << 16);
-        lg[3] += __uint_as_float(sv.y & 0xFFFF0000u);
-      }
-    } else {
-      // this lane's 8 channels (of slice c / cout), then the sum over the
-      // row's groups (consecutive lanes, all active: a row is in range for
-      // all or none)
-      const int c = grp * 8, sl = c / cout, cl = c - sl * cout;
-      float v[8];
-      sum8((tile << hsl) | sl, bias + (size_t)sl * (F8 ? 2 : 1) * cout, cl, v);
-#pragma unroll
-      for (int o2 = 0; o2 < 4; ++o2) lg[o2] = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float a = F8 ? e4m3_round(act_fn<ACT>(v[e])) : bf16_round(act_fn<ACT>(v[e]));
-#pragma unroll
-        for (int o2 = 0; o2 < 4; ++o2) lg[o2] += head_w[o2 * (cout << hsl) + c + e] * a;
-      }
-      for (int m = groups >> 1; m >= 1; m >>= 1)
-#pragma unroll
-        for (int o2 = 0; o2 < 4; ++o2) lg[o2] += __shfl_xor(lg[o2], m);
-      if (grp != 0) return;
-#pragma unroll
-      for (int o2 = 0; o2 < 4; ++o2) lg[o2] += head_b[o2];
-    }
-    const int HH = g.H * g.H;
-    const int s = i * g.H + j;
-    nib[(long long)b * g.V + (long long)t * HH + s] = (uint8_t)flip_nibble(g, tables, i, j, lg);
-    if (logits) {
-#pragma unroll
-      for (int o2 = 0; o2 < 4; ++o2) logits[(((long long)b * 4 + o2) * g.T + t) * HH + s] = lg[o2];
-    }
-  }
-}
-
 // Launches one instance of the hidden kernel (the LDS size attribute set on
 // its first use).
 template <int CIN, int COUT, int EPI, int MODE, bool F8, int KS>
-hipError_t launch_hidden(const Geom& g, const Tiling& tl, int act, const void* x, void* y, int ystride,
-                         const void* wfrag, const float* bias, const float* head_w, const float* head_b,
-                         const int32_t* tables, uint8_t* nib, float* logits, int batch, int n_workgroups,
-                         int kshift, float* partial, const uint16_t* sc, int sc_stride, int lsl,
-                         uint32_t* sched, hipStream_t stream) {
+hipError_t launch_one(const HiddenCall& c) {
   using L = Lds<COUT, KS>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)conv_hidden_kernel<CIN, COUT, EPI, MODE, F8, KS>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, L::total);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  const long long nunits = tl.ntiles << (kshift + lsl);
-  const long long nwg = conv_workgroups(nunits, n_workgroups);
-  if (nunits <= 2 * nwg) sched = nullptr;  // every unit is one of the two fixed ones
+  static const hipError_t attr = hipFuncSetAttribute((const void*)conv_hidden_kernel<CIN, COUT, EPI, MODE, F8, KS>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, L::total);
+  if (attr != hipSuccess) return attr;
+  const Tiling& tl = *c.tl;
+  const long long nunits = tl.ntiles << c.lsl;
+  const long long nwg = conv_workgroups(nunits, c.n_workgroups);
+  uint32_t* const sched = nunits <= 2 * nwg ? nullptr : c.sched;  // null: every unit is one of the two fixed ones
   // fixed units per workgroup before the counters: two on cells; on flat
   // tiles seven eighths of a workgroup's share
   const long long share = (nunits + 7) / 8 / (nwg / 8);
   const int nstat = tl.mode == 0 ? (int)std::max(2ll, share * 7 / 8) : 2;
   hipLaunchKernelGGL((conv_hidden_kernel<CIN, COUT, EPI, MODE, F8, KS>), dim3((unsigned)nwg), dim3(NT),
-                     (size_t)L::total, stream, g, tl, act, x, y, ystride, (const u32x4*)wfrag, bias, head_w,
-                     head_b, tables, nib, logits, batch, kshift, partial, sc, sc_stride, lsl, sched, nstat);
-  return hipSuccess;
-}
-
-template <int CIN, int COUT, int EPI, int MODE, bool F8, int KS>
-hipError_t launch_one(const HiddenCall& c) {
-  const Geom& g = *c.g;
-  const Tiling& tl = *c.tl;
-  const Split_k& sk = *c.sk;
-  hipError_t e;
-  // a head over output slices (a small batch): every unit parks its
-  // slice's sums, and the second kernel finishes whole rows, head and
-  // threshold included (32-channel slices exist only for this)
-  constexpr bool PARK_ONLY = EPI == EPI_HEAD && COUT == 32;
-  if constexpr (!PARK_ONLY) {
-    if (sk.kshift == 0 && !(EPI == EPI_HEAD && sk.lsl > 0)) {
-      e = launch_hidden<CIN, COUT, EPI, MODE, F8, KS>(g, tl, c.act, c.x, c.y, c.ystride, c.wfrag, c.bias, c.head_w,
-                                                      c.head_b, c.tables, c.nib, c.logits, c.batch, c.n_workgroups, 0,
-                                                      nullptr, c.sc, c.sc_stride, sk.lsl, sk.sched, c.stream);
-      return e != hipSuccess ? e : hipGetLastError();
-    }
-  }
-  // K loops split: park the parts, then add them and finish the tiles
-  e = launch_hidden<CIN, COUT, EPI_PARK, MODE, F8, KS>(g, tl, c.act, c.x, c.y, c.ystride, c.wfrag, c.bias, c.head_w,
-                                                       c.head_b, c.tables, c.nib, c.logits, c.batch, c.n_workgroups,
-                                                       sk.kshift, sk.partial, nullptr, 0, sk.lsl, sk.sched, c.stream);
-  if (e != hipSuccess) return e;
-  const long long threads = ((long long)tl.ntiles << sk.lsl) * kTileRows *
-                            (EPI == EPI_ACT || EPI == EPI_ADD || EPI == EPI_HEAD ? COUT / 8 : 1);
-  static_assert(EPI != EPI_HEAD || (64 % (COUT / 8) == 0), "a row's head lanes lie in one wave");
-  if (EPI == EPI_HEAD && (COUT << sk.lsl) / 8 > 64) return hipErrorInvalidValue;
-  with_activation(c.act, [&](auto A) {
-    hipLaunchKernelGGL((split_finish_kernel<EPI, decltype(A)::value, F8>), dim3((unsigned)((threads + 255) / 256)),
-                       dim3(256), 0, c.stream, g, tl, COUT, sk.kshift, sk.partial, c.bias, c.y, c.ystride, c.head_w,
-                       c.head_b, c.tables, c.nib, c.logits, c.batch, c.sc, c.sc_stride, sk.lsl);
-  });
+                     (size_t)L::total, c.stream, *c.g, tl, c.act, c.x, c.y, c.ystride, (const u32x4*)c.wfrag, c.bias,
+                     c.head_w, c.head_b, c.tables, c.nib, c.logits, c.batch, c.sc, c.sc_stride, c.lsl, sched, nstat);
   return hipGetLastError();
 }
 

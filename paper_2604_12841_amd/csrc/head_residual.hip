@@ -8,8 +8,9 @@
 // stabilizer sits (or is drawn, in the paper's layout), channel 3 likewise
 // for Z.  The four flip bits of a voxel are kept as one nibble per voxel in a
 // small workspace; fp32 logits are written only when asked for.  (Used by
-// one-hidden-layer bf16 networks on the paper's layout; elsewhere the head is
-// fused into the last hidden layer.)
+// one-hidden-layer bf16 networks on the paper's layout and by small launches
+// of 128-wide networks; elsewhere the head is fused into the last hidden
+// layer.)
 //
 // K5 (residual + repack): a wave64 builds one packed 64-bit output word at a
 // time from nibble rows staged in LDS.  Lane l computes bit 64 w + l of
@@ -26,43 +27,56 @@ namespace pd {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
+// A voxel's row of activations (bf16, or F8 E4M3 codes) is read 16 bytes per
+// lane by consecutive lanes, whose partial sums of the four logits are then
+// added; the first of them thresholds and stores.  cin: 64 or 128, so a row
+// is 4, 8 or 16 lanes.
+template <bool F8>
 __global__ void __launch_bounds__(256) head_kernel(Geom g, int cin, const void* __restrict__ x,
-                                                   const float* __restrict__ w_head,
-                                                   const float* __restrict__ b_head,
-                                                   const int32_t* __restrict__ tables,
-                                                   uint8_t* __restrict__ nib, float* __restrict__ logits,
-                                                   int batch) {
-  __shared__ float w[4 * 128];
-  for (int e = threadIdx.x; e < 4 * cin; e += blockDim.x) w[e] = w_head[e];
-  __syncthreads();
-  long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long long)batch * g.V) return;
-  const int b = (int)(gid / g.V);
-  const int v = (int)(gid - (long long)b * g.V);
+                                                   const float* __restrict__ w_head, const float* __restrict__ b_head,
+                                                   const int32_t* __restrict__ tables, uint8_t* __restrict__ nib,
+                                                   float* __restrict__ logits, int batch) {
+  constexpr int CPL = F8 ? 16 : 8;  // channels per lane
+  const int lpr = cin / CPL;        // lanes per row (a power of two)
+  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long u = gid / lpr;
+  const bool real = u < (long long)batch * g.V;
+  const int c0 = (int)(gid - u * lpr) * CPL;
+  const int b = (int)((real ? u : 0) / g.V);
+  const int v = (int)((real ? u : 0) - (long long)b * g.V);
   const int HH = g.H * g.H;
   const int t = v / HH, s = v - t * HH;
   const int i = s / g.H, j = s - i * g.H;
-  const long long p = padded_index(g, b, t, i, j);
-  float acc[4] = {b_head[0], b_head[1], b_head[2], b_head[3]};
-  const u32x4* xr = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(x) + p * cin);
-  for (int c8 = 0; c8 < cin / 8; ++c8) {
-    u32x4 q = xr[c8];
+  const u32x4 q = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(x) +
+                                                  (padded_index(g, b, t, i, j) * cin + c0) * (F8 ? 1 : 2));
+  float a[CPL];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      float lo = __uint_as_float(q[h] << 16);
-      float hi = __uint_as_float(q[h] & 0xffff0000u);
-      const int c = c8 * 8 + 2 * h;
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        acc[o] = fmaf(w[o * cin + c], lo, acc[o]);
-        acc[o] = fmaf(w[o * cin + c + 1], hi, acc[o]);
-      }
+  for (int h = 0; h < 4; ++h) {
+    if constexpr (F8) {
+      a[4 * h] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 0);
+      a[4 * h + 1] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 1);
+      a[4 * h + 2] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 2);
+      a[4 * h + 3] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 3);
+    } else {
+      a[2 * h] = __uint_as_float(q[h] << 16);
+      a[2 * h + 1] = __uint_as_float(q[h] & 0xffff0000u);
     }
   }
-  nib[gid] = (uint8_t)flip_nibble(g, tables, i, j, acc);
+  float lg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int e = 0; e < CPL; ++e)
+#pragma unroll
+    for (int o = 0; o < 4; ++o) lg[o] = fmaf(w_head[o * cin + c0 + e], a[e], lg[o]);
+  for (int m = lpr >> 1; m >= 1; m >>= 1)
+#pragma unroll
+    for (int o = 0; o < 4; ++o) lg[o] += __shfl_xor(lg[o], m);
+  if (!real || c0 != 0) return;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) lg[o] += b_head[o];
+  nib[u] = (uint8_t)flip_nibble(g, tables, i, j, lg);
   if (logits) {
 #pragma unroll
-    for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + s] = acc[o];
+    for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + s] = lg[o];
   }
 }
 
@@ -256,12 +270,17 @@ __global__ void __launch_bounds__(256) residual_from_flips_kernel(Geom g, const 
   if (lane == 0) residual[(long long)b * g.Wd + w] = m;
 }
 
-hipError_t launch_head(const Geom& g, int cin, const void* x, const float* w_head, const float* b_head,
+hipError_t launch_head(const Geom& g, int cin, const void* x, int fp8, const float* w_head, const float* b_head,
                        const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream) {
-  long long total = (long long)batch * g.V;
-  unsigned grid = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL(head_kernel, dim3(grid), dim3(256), 0, stream, g, cin, x, w_head, b_head, tables, nib, logits,
-                     batch);
+  if (cin != 64 && cin != 128) return hipErrorInvalidValue;
+  const long long threads = (long long)batch * g.V * (cin / (fp8 ? 16 : 8));
+  const dim3 grid((unsigned)((threads + 255) / 256));
+  if (fp8)
+    hipLaunchKernelGGL(head_kernel<true>, grid, dim3(256), 0, stream, g, cin, x, w_head, b_head, tables, nib, logits,
+                       batch);
+  else
+    hipLaunchKernelGGL(head_kernel<false>, grid, dim3(256), 0, stream, g, cin, x, w_head, b_head, tables, nib, logits,
+                       batch);
   return hipGetLastError();
 }
 

@@ -161,51 +161,8 @@ hipError_t launch_conv_single(const Geom& g, const Tiling& tl, int cout, int act
                               int n_workgroups, hipStream_t stream);
 int conv_single_max_span();  // staged voxels a tile may need
 
-// A 3x3x3 layer on the zero-halo activations x (c_in in {64, 128, 256}),
-// bf16, or fp8 (E4M3 activations and weight codes, bias holding c_out
-// biases then c_out per-channel weight scales, one byte per value in x and
-// y, fragments of conv_fragments_fp8 in 32-channel chunks).
-//   head == 0: a hidden layer (c_out in {64, 128}) writing y, whose voxel rows
-//              are ystride channels apart (a 256-wide layer runs as two slices
-//              of 128, y pointing at the slice's first channel);
-//   head == 1: a hidden layer whose epilogue applies the 1x1x1 head and the
-//              threshold as launch_conv_single does, instead of writing y;
-//   head == 2: the output layer itself (c_out = 4, no activation): its
-//              outputs are the logits, thresholded into flip nibbles; with
-//              sc non-null, the 4 bf16 channels of sc's row (sc_stride
-//              values apart) are added to the logits first;
-//   head == 4: a hidden layer with sc's row (bf16, sc_stride values apart,
-//              pointing at the slice's first channel) added to the
-//              pre-activation (residual blocks; bf16 only).
-// Weight fragments in 16-channel chunks (conv_fragments in api.hip; c_out = 4
-// padded to 32 channels, bias to 32 values); n_workgroups =
-// conv_hidden_workgroups_per_cu() per CU.
-// Small batches: each tile's K loop (its channel chunks) split into
-// 2^kshift parts run by different workgroups of one launch, which park fp32
-// sums in `partial` (max_units units of conv_hidden_partial_floats_per_unit()
-// floats); a second launch adds each tile's parts in part order and runs the
-// epilogue.  kshift = 0: no split, one launch.
-struct Split_k {
-  int kshift;
-  float* partial;
-  long long max_units;
-  int lsl = 0;  // 2^lsl output-channel slices of c_out channels in one launch
-  // 256 zeroed words (per XCD: a grab and a done counter, 64 bytes apart):
-  // a launch of more than two units per workgroup takes its units after the
-  // fixed ones from these counters and leaves them zero; null: fixed shares
-  uint32_t* sched = nullptr;
-};
-
-// ks: kernel size 3, or 5 (cell tiles, a halo of two; bf16 c_in / c_out of
-// 64 or 128, activations and the output layer).
-hipError_t launch_conv_hidden(const Geom& g, const Tiling& tl, int cin, int cout, int act, const void* x,
-                              void* y, int ystride, const void* wfrag, const float* bias, int head,
-                              const float* head_w, const float* head_b, const int32_t* tables, uint8_t* nib,
-                              float* logits, int batch, int n_workgroups, const Split_k& sk, int fp8,
-                              const uint16_t* sc, int sc_stride, int ks, hipStream_t stream);
+// The hidden layers' kernels take a HiddenCall (conv_hidden.h).
 int conv_hidden_max_span(int ks);         // staged voxels a tile may need
-int conv_hidden_chunk_channels(int fp8);  // input channels per K-loop chunk
-size_t conv_hidden_partial_floats_per_unit();
 int conv_hidden_workgroups_per_cu(int ks);
 
 // The 3x3x3 output layer of four filters with the threshold (and the last
@@ -267,11 +224,10 @@ hipError_t launch_stream_scatter(const StreamWindow* win, const uint64_t* const*
 
 // predecoder_run of handle h with its workspace laid out in the `bytes` of
 // device memory at `base` instead of the handle's own (input planes,
-// activation buffers, projection outputs, flip nibbles, then as many units of
-// parked split-K sums as fit, at most the handle's own number): the planes
-// and activation buffers are cleared with a fill kernel first; nothing is
-// allocated.  PD_ERR_TOO_LARGE when the regions before the parked sums do not
-// fit.  Asynchronous on st.
+// activation buffers, projection outputs, flip nibbles): the planes and
+// activation buffers are cleared with a fill kernel first; nothing is
+// allocated.  PD_ERR_TOO_LARGE when the regions do not fit.  Asynchronous on
+// st.
 pd_status run_in_region(pd_predecoder* h, hipStream_t st, const uint64_t* det, int batch, uint64_t* flips,
                         uint64_t* residual, float* logits, void* base, size_t bytes);
 
@@ -295,8 +251,9 @@ hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const flo
                             hipStream_t stream);
 std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout);
 
-// The 1x1x1 head and the threshold over bf16 activation rows of c_in values.
-hipError_t launch_head(const Geom& g, int cin, const void* x, const float* w_head, const float* b_head,
+// The 1x1x1 head and the threshold over activation rows of c_in (64 or 128)
+// values, bf16 or E4M3.
+hipError_t launch_head(const Geom& g, int cin, const void* x, int fp8, const float* w_head, const float* b_head,
                        const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream);
 
 hipError_t launch_residual_pack(const Geom& g, const int32_t* tables, const uint64_t* det,

@@ -26,7 +26,7 @@ __host__ __device__ inline CellTile cell_tile(const Tiling& tl, int tile) {
   return ct;
 }
 
-// Voxel u of a cell, in (t, i, j) order: its round, row and column in the cell.
+// Voxel u of a cell, in (t, i, j) order (of any tile size): its round, row and column in the cell.
 __host__ __device__ inline void cell_voxel(const Tiling& tl, int u, int* a, int* c, int* e) {
   const int bij = tl.BI * tl.BJ;
   *a = (int)fdiv((uint32_t)u, tl.dv_bij);
