@@ -730,15 +730,16 @@ int conv_parts(const pd_predecoder* h, const LayerRun& L, long long tiles) {
 // 27 / 48, fp8 19 / 32).
 
 // Small launches: a workgroup costs `fixed` (start, staging, the sums'
-// exchange, epilogue) and `piece` per 128-byte piece of its input rows.  Where
-// two fit a CU, a further one costs less than the first.  kg: K groups, which
-// the parts fill up to four (fp8: always four).
+// exchange, epilogue) and `piece` per 128-byte piece of its input rows; where
+// two fit a CU, each adds `share` of its pieces' time (64 x 64 tiles of one K
+// group are bound by L1 and LDS and gain nothing by sharing).  kg: K groups,
+// which the parts fill up to four (fp8: always four).
 struct SmallShape {
   int kg, rows, cols, acc;  // acc: accumulator registers of a lane
-  double fixed, piece;
+  double fixed, piece, share = 0.82;
 };
 constexpr SmallShape kSmallBf16[] = {
-    {1, 64, 64, 16, 4.5, 3.7},  {1, 128, 64, 32, 4.3, 7.3}, {1, 128, 128, 64, 6.0, 9.5},
+    {1, 64, 64, 16, 4.5, 3.7, 1.1}, {1, 128, 64, 32, 4.3, 7.3}, {1, 128, 128, 64, 6.0, 9.5},
     {2, 64, 32, 16, 3.9, 2.7},  {2, 64, 64, 32, 4.0, 5.0},  {2, 128, 64, 64, 4.5, 5.0},
     {4, 64, 32, 32, 3.9, 1.65}, {4, 64, 64, 64, 3.6, 2.7},  {4, 128, 32, 64, 4.0, 3.0}};
 constexpr SmallShape kSmallFp8[] = {{4, 64, 32, 32, 4.5, 1.35}, {4, 64, 64, 64, 4.4, 2.35}, {4, 128, 64, 128, 5.4, 4.4}};
@@ -764,7 +765,7 @@ double small_us(const pd_predecoder* h, const LayerRun& L, int batch, int parts,
     const double pieces = row < 128 ? 0.8 : row / 128.0;
     const double us = per_cu == 1 ? rounds * (s.fixed + s.piece * pieces)
                                   : s.fixed * (1.0 + 0.75 * (rounds - 1)) +
-                                        s.piece * pieces * (turns == 1 ? 1.0 : 0.82 * turns);
+                                        s.piece * pieces * (turns == 1 ? 1.0 : s.share * turns);
     if (us < best) {
       best = us;
       *plan = {s.rows, s.cols, parts};
