@@ -963,13 +963,9 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
     {
       const int nsl = B.c_mid > 128 ? B.c_mid / 128 : 1, cw = B.c_mid / nsl;
       if (k == 0) {
-        for (int q = 0; q < nsl && s == PD_OK; ++q) {
-          const void* wq = (const char*)h->wdev[2 * k] + q * h->wslice[2 * k];
-          void* yq = (char*)hb + (size_t)q * cw * ae;
-          // layer 1 (fp8: bf16 matrix work on the dequantised weights, E4M3 output)
-          s = check_launch(pd::launch_conv_first(g, B.c_in, cw, B.act, x, yq, B.c_mid, wq, h->bdev[2 * k] + q * cw,
-                                                 batch, fp8, 3, st));
-        }
+        // layer 1 (fp8: bf16 matrix work on the dequantised weights, E4M3 output)
+        s = check_launch(pd::launch_conv_first(g, B.c_in, cw, nsl, h->wslice[2 * k], B.act, x, nullptr, hb, B.c_mid,
+                                               h->wdev[2 * k], h->bdev[2 * k], batch, fp8, 3, st));
       } else {
         LayerRun L{B.c_in, B.c_mid, cw, B.act, x, hb, h->wdev[2 * k], h->bdev[2 * k]};
         s = run_hidden(h, ws, L, nullptr, batch, st);
@@ -1055,7 +1051,10 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
   };
   pd_status s;
   if ((s = mark()) != PD_OK) return s;
-  s = check_launch(pd::launch_unpack(g, h->tables, det, batch, ws.planes, 1, fp32, st));
+  // (small launches: layer 1 unpacks the events itself)
+  const bool single = n == 2 && !out3 && h->layers[0].c_in == 2 && stop < 0;  // layer 1 carries the head
+  const bool fused = !fp32 && !single && pd::conv_first_fuses(g, batch, ks);
+  if (!fused) s = check_launch(pd::launch_unpack(g, h->tables, det, batch, ws.planes, 1, fp32, st));
   if (s != PD_OK) return s;
   const void* x = ws.planes;
   Tiling tl = h->tiling;
@@ -1080,16 +1079,12 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
     } else {
       // a 256-wide layer runs as two slices of 128 output channels over the
       // same input (slice k: its fragments, biases (fp8: and scales) and
-      // output channels): two launches of layer 1's kernel, one of the
-      // hidden kernel
+      // output channels)
       const int nsl = h->wslice[l] ? 2 : 1, cw = L.c_out / nsl;
       if (l == 0) {
-        for (int k = 0; k < nsl && s == PD_OK; ++k) {
-          const void* wk = (const char*)h->wdev[l] + k * h->wslice[l];
-          void* yk = (char*)y + (size_t)k * cw * aelem;
-          s = check_launch(pd::launch_conv_first(g, L.c_in, cw, L.act, x, yk, L.c_out, wk, h->bdev[l] + k * cw,
-                                                 batch, fp8, ks, st));
-        }
+        const pd::PackedEvents pe{h->tables, det};
+        s = check_launch(pd::launch_conv_first(g, L.c_in, cw, nsl, h->wslice[l], L.act, x, fused ? &pe : nullptr, y,
+                                               L.c_out, h->wdev[l], h->bdev[l], batch, fp8, ks, st));
       } else {  // the last hidden layer may carry the head and the threshold in its epilogue
         LayerRun R{L.c_in, L.c_out, cw, L.act, x, y, h->wdev[l], h->bdev[l], fuse_head ? 1 : 0, h->head_w, h->head_b,
                    head_layer};

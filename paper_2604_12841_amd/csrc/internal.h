@@ -141,15 +141,22 @@ hipError_t launch_unpack(const Geom& g, const int32_t* tables, const uint64_t* d
 // The first 3x3x3 layer (c_in = 2 or 4, c_out = 64 or 128) when it is not
 // also the last hidden layer: planes [batch * S][c_in] bf16, weight fragments
 // [ceil(27 c_in / 16) k-steps][c_out / 32][64 lanes][8 bf16].  Output voxel
-// rows are ystride channels apart (a wider layer is run as slices of c_out
-// channels, y pointing at the slice's first channel).
+// rows are ystride channels apart; a wider layer runs as `slices` slices of
+// c_out channels, their fragments wslice bytes apart.
+// pe: non-null on launches that conv_first_fuses allows: the packed detector
+// events to read in place of planes.
 // fp8: y holds E4M3 codes (one byte per value; the planes and the bf16
 // weight fragments are unchanged, the weights being E4M3 values times their
 // power-of-two scales, which bf16 represents exactly).
 // ks: kernel size 3, or 5 (c_in = 4, bf16, a halo of two).
-hipError_t launch_conv_first(const Geom& g, int cin, int cout, int act, const void* planes, void* y,
-                             int ystride, const void* wfrag, const float* bias, int batch, int fp8, int ks,
-                             hipStream_t stream);
+struct PackedEvents {
+  const int32_t* tables;
+  const uint64_t* det;
+};
+hipError_t launch_conv_first(const Geom& g, int cin, int cout, int slices, size_t wslice, int act, const void* planes,
+                             const PackedEvents* pe, void* y, int ystride, const void* wfrag, const float* bias,
+                             int batch, int fp8, int ks, hipStream_t stream);
+bool conv_first_fuses(const Geom& g, int batch, int ks);
 
 // A network with one hidden layer: layer 1 (as launch_conv_first) with the
 // 1x1x1 head (head_w [4][cout] fp32, bf16-valued; head_b [4]) and the
