@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -113,6 +114,8 @@ Geom make_geom(int d, int T, int layout = PD_LAYOUT_PLAQUETTE, int first = PD_BO
   g.layout = layout;
   g.first = first;
   g.last = last;
+  g.first_n = INT_MAX;
+  g.last_from = 0;
   g.pad = pad;
   g.H = layout == PD_LAYOUT_PAPER ? d : d + 1;  // the data qubits, or the plaquettes
   g.Wp = g.H + 2 * pad;
@@ -861,17 +864,51 @@ pd_status run_big(const pd_predecoder* h, Workspace& ws, const LayerRun& L, floa
   return check_launch(pd::launch_conv_hidden(c, h->dtype == PD_DTYPE_FP8));
 }
 
-// One hidden layer over the batch.  When its units fill the persistent
-// kernel's slots one to four times over and leave a short remainder, which
-// would take a whole unit's time with most of the chip idle, the first
-// samples, whose units fill whole rounds, run there and the last few, with
-// their sums in parts, on the small-launch kernel -- for long units only
-// (512 input channels in bf16): the second launch and the shorter batch's
-// parts cost about 45 us.  (Model 6 at 13^3, batch 16: 552 units on 512
-// slots, the last 2 samples.)
+// The sums of a layer over a batch: samples 0 .. first - 1 in `parts` parts,
+// the rest in tail_parts.  When the units fill the persistent kernel's slots
+// one to four times over and leave a short remainder, which would take a
+// whole unit's time with most of the chip idle, the last few samples take
+// parts and run on the small-launch kernel -- for long units only (512 input
+// channels in bf16): the second launch and the parts cost about 45 us.
+// (Model 6 at 13^3, batch 16: 552 units on 512 slots, the last 2 samples.)
 constexpr long long kMaxTailRounds = 4;  // past this, a remainder costs little
 constexpr double kTailCostUs = 45.0;
 
+struct SumPlan {
+  int parts, first, tail_parts;
+};
+
+SumPlan sum_plan(const pd_predecoder* h, const LayerRun& L, int batch) {
+  const int nsl = L.cout / L.cw;
+  auto tiles_of = [&](int nb) {
+    Tiling t = h->tiling;
+    tiling_for_batch(&t, h->g, nb);
+    return t.ntiles;
+  };
+  const long long tiles = tiles_of(batch), units = tiles * nsl;
+  const long long round = (long long)h->n_cu * pd::conv_hidden_workgroups_per_cu(h->ks), q = units / round;
+  SumPlan p{h->dtype == PD_DTYPE_FP8 ? 1 : conv_parts(h, L, tiles), batch, 1};
+  if (p.parts == 1 && q >= 1 && q <= kMaxTailRounds && units % round != 0) {
+    // the most first samples whose tiles fit q full rounds (tiles grow with
+    // the batch: per sample, or one flat run of batch x V voxels)
+    const Tiling& base = h->tiling;
+    const long long fit = q * round / nsl;  // tiles
+    const bool flat = base.mode == 0 && (base.seg_len < 0 || base.tiles_per_seg == 0);
+    const long long per = base.mode == 1 ? (long long)base.ntT * base.ntI * base.ntJ : base.tiles_per_seg;
+    const long long first = flat ? fit * pd::kTileRows / h->g.V : fit / per;
+    if (first >= 1 && first < batch) {
+      double unit_us = 0.0;
+      const int tail_parts = split_parts(h, tiles_of(batch - (int)first), L.cin, L.cw, nsl, &unit_us);
+      if (tail_parts > 1 && unit_us * (1.0 - 1.0 / tail_parts) > kTailCostUs) {
+        p.first = (int)first;
+        p.tail_parts = tail_parts;
+      }
+    }
+  }
+  return p;
+}
+
+// One hidden layer over the batch.
 pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, float* logits, int batch,
                      hipStream_t st) {
   pd::SmallPlan plan{};
@@ -879,41 +916,19 @@ pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, f
     (void)small_us(h, L, batch, 4, &plan);
     return run_small(h, ws, L, plan, logits, 0, batch, st);
   }
-  const int nsl = L.cout / L.cw;
   const BigTime bt = big_time(h, L);
-  auto tiles_of = [&](int nb) {
-    Tiling t = h->tiling;
-    tiling_for_batch(&t, h->g, nb);
-    return t.ntiles;
-  };
   // samples b0 .. b0 + nb - 1 with sums of `parts` parts
   auto run = [&](int b0, int nb, int parts) {
     const double small = small_us(h, L, nb, parts, &plan);
-    if (parts > 1 || small * 1.05 < big_us(bt, tiles_of(nb) * nsl)) return run_small(h, ws, L, plan, logits, b0, nb, st);
+    Tiling t = h->tiling;
+    tiling_for_batch(&t, h->g, nb);
+    if (parts > 1 || b0 > 0 || small * 1.05 < big_us(bt, t.ntiles * (L.cout / L.cw)))
+      return run_small(h, ws, L, plan, logits, b0, nb, st);
     return run_big(h, ws, L, logits, nb, st);
   };
-  const long long tiles = tiles_of(batch), units = tiles * nsl, q = units / bt.round;
-  const bool fp8 = h->dtype == PD_DTYPE_FP8;
-  const int parts = fp8 ? 1 : conv_parts(h, L, tiles);
-  if (parts == 1 && q >= 1 && q <= kMaxTailRounds && units % bt.round != 0) {
-    // the most first samples whose tiles fit q full rounds (tiles grow with
-    // the batch: per sample, or one flat run of batch x V voxels)
-    const Tiling& base = h->tiling;
-    const long long fit = q * bt.round / nsl;  // tiles
-    const bool flat = base.mode == 0 && (base.seg_len < 0 || base.tiles_per_seg == 0);
-    const long long per = base.mode == 1 ? (long long)base.ntT * base.ntI * base.ntJ : base.tiles_per_seg;
-    const long long first = flat ? fit * pd::kTileRows / h->g.V : fit / per;
-    if (first >= 1 && first < batch) {
-      const int nb = batch - (int)first;
-      double unit_us = 0.0;
-      const int tail_parts = split_parts(h, tiles_of(nb), L.cin, L.cw, nsl, &unit_us);
-      if (tail_parts > 1 && unit_us * (1.0 - 1.0 / tail_parts) > kTailCostUs) {
-        const pd_status s = run(0, (int)first, 1);
-        return s != PD_OK ? s : run((int)first, nb, tail_parts);
-      }
-    }
-  }
-  return run(0, batch, parts);
+  const SumPlan sp = sum_plan(h, L, batch);
+  const pd_status s = run(0, sp.first, sp.parts);
+  return s != PD_OK || sp.first == batch ? s : run(sp.first, batch - sp.first, sp.tail_parts);
 }
 
 // The path of a residual network (Model 6, Sec. VI, Fig. Model8Representation):
@@ -1849,6 +1864,32 @@ struct pd_stream {
 };
 
 namespace {
+// Whether every hidden layer of a plain network sums `batch` samples of T
+// rounds in the parts that a batch of T2 rounds takes (no sample apart).
+bool same_sums(const pd_layer* layers, int n, int dtype, int layout, int d, int T, int batch, int T2, int batch2,
+               int n_cu) {
+  if (dtype != PD_DTYPE_BF16) return true;  // (fp32 sums do not depend on the batch; fp8 ones may)
+  pd_predecoder h[2];
+  const int Ts[2] = {T, T2}, Bs[2] = {batch, batch2};
+  for (int k = 0; k < 2; ++k) {
+    h[k].ks = network_ks(layers);
+    h[k].g = make_geom(d, Ts[k], layout, 0, 0, (h[k].ks - 1) / 2);
+    h[k].dtype = dtype;
+    h[k].n_cu = n_cu;
+    h[k].tiling = plan_tiling(h[k].g, Bs[k], h[k].ks);
+  }
+  for (int l = 1; l < n - 1; ++l) {
+    LayerRun L{};
+    L.cin = layers[l].c_in;
+    L.cout = layers[l].c_out;
+    L.cw = std::min(L.cout, 128);
+    L.carries_head = l == n - 2 && layers[n - 1].k == 1;
+    const SumPlan a = sum_plan(&h[0], L, batch), b = sum_plan(&h[1], L, batch2);
+    if (a.parts != b.parts || a.first != batch || b.first != batch2) return false;
+  }
+  return true;
+}
+
 void stream_free(pd_stream* s) {
   for (auto& g : s->groups) {
     if (g.h) predecoder_destroy(g.h);
@@ -1900,6 +1941,43 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
     }
     s->win[k] = pd::StreamWindow{st[k], ln[k], cs[k], cl[k], gi, s->groups[gi].count++};
   }
+  // All windows as one batch of the longest window's length: the shorter ones,
+  // at the stream's ends, read further rounds that their cores do not depend
+  // on (the buffer reaches the receptive field), and the geometric channels
+  // are cleared for the first / last windows' samples.  One run then takes
+  // the place of up to five, four of them a few windows each (Model 4, d =
+  // 13, two streams of 1000 rounds, bf16: 3.38 -> 2.89 ms).  Only where no sum's parts
+  // change.
+  int reach = 0;
+  for (int l = 0; l < n_layers; ++l) reach += (layers[l].k - 1) / 2;
+  int n_cu = 0, dev = 0;
+  bool merge = keys.size() > 1 && buffer >= reach && layer_chain_ok(layers, n_layers, o.layout) &&
+               hipGetDevice(&dev) == hipSuccess &&
+               hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n_cu > 0;
+  const int len = *std::max_element(ln.begin(), ln.end());
+  if (merge) {
+    const Geom whole = make_geom(d, len, o.layout, 0, 0, (network_ks(layers) - 1) / 2);
+    merge = supported(whole, layers, n_layers, dtype) && (long long)nw * n_streams * whole.S < (1ll << 30);
+    for (const auto& G : s->groups)
+      merge = merge && same_sums(layers, n_layers, dtype, o.layout, d, G.len, G.count * n_streams, len, nw * n_streams,
+                                 n_cu);
+  }
+  int first_n = INT_MAX, last_from = 0;
+  if (merge) {
+    keys.assign(1, {len, 1, 1});
+    s->groups.assign(1, pd_stream::Group());
+    s->groups[0].len = len;
+    s->groups[0].count = nw;
+    int firsts = 0, lasts = 0;
+    for (int k = 0; k < nw; ++k) {
+      const int start = std::min(st[k], n_rounds - len);
+      firsts += start == 0;
+      lasts += start + len == n_rounds;
+      s->win[k] = pd::StreamWindow{start, len, cs[k], cl[k], 0, k};
+    }
+    first_n = firsts * n_streams;
+    last_from = (nw - lasts) * n_streams;
+  }
   pd_status r = PD_OK;
   auto fail = [&](pd_status e) {
     stream_free(s);
@@ -1912,6 +1990,8 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
     if (!keys[gi][2]) go.last_round = PD_BOUNDARY_NONE;
     r = predecoder_create_ex(weights, n_weights, d, G.len, layers, n_layers, dtype, G.count * n_streams, &go, &G.h);
     if (r != PD_OK) return fail(r);
+    G.h->g.first_n = first_n;
+    G.h->g.last_from = last_from;
     const size_t rows = (size_t)G.count * n_streams;
     if ((r = dev_alloc(&G.det, rows * predecoder_det_words(d, G.len) * 8)) != PD_OK) return fail(r);
     if ((r = dev_alloc(&G.flips, rows * predecoder_flip_words(d, G.len) * 8)) != PD_OK) return fail(r);

@@ -108,7 +108,9 @@ __device__ __forceinline__ u32x2 unpack_voxel(const Geom& g, const Packed& pk, i
     if constexpr (CIN == 4) {
       // weight / 4 of the stabilizer drawn here (1 or 0.5), cleared in the boundary rounds
       auto present = [&](int n, int kind) -> unsigned {
-        if (n < 0 || (t == 0 && g.first == kind) || (t == g.T - 1 && g.last == kind)) return 0u;
+        if (n < 0 || (t == 0 && g.first == kind && b < g.first_n) ||
+            (t == g.T - 1 && g.last == kind && b >= g.last_from))
+          return 0u;
         return pk.tables[tables_supp(g) + n * 4 + 2] >= 0 ? 0x3F80u : 0x3F00u;
       };
       out.y = present(nx, 1) | present(nz, 2) << 16;

@@ -39,6 +39,9 @@ struct Geom {
   // 2 X): in the paper's layout, Z clears x_present and X clears z_present
   // in that round.
   int first, last;
+  // ... for samples b < first_n / b >= last_from only (a stream's windows in
+  // one batch: those at the stream's ends)
+  int first_n, last_from;
 };
 
 __host__ __device__ inline long long padded_index(const Geom& g, int b, int t, int i, int j) {

@@ -68,17 +68,21 @@ __global__ void __launch_bounds__(256) unpack_kernel(Geom g, const int32_t* __re
   const int s = v - t * HH;
   const int nx = tables[tables_comp_x(g) + s], nz = tables[tables_comp_z(g) + s];
   float px = 0.0f, pz = 0.0f;
+  // the basis cleared in this round, by its boundary kind (0: none), for samples before first_n / from last_from on
+  const int cf = t == 0 ? g.first : 0, cl = t == g.T - 1 ? g.last : 0;
   if constexpr (PAPER) {
     // weight / 4 of the stabilizer drawn here: 1 for four qubits, 0.5 for two
-    auto present = [&](int n, int kind) -> float {
+    auto present = [&](int n) -> float {
       if (n < 0) return 0.0f;
-      if ((t == 0 && g.first == kind) || (t == g.T - 1 && g.last == kind)) return 0.0f;
       const int32_t* sp = tables + tables_supp(g) + n * 4;
       return (sp[2] >= 0) ? 1.0f : 0.5f;
     };
-    px = present(nx, 1);
-    pz = present(nz, 2);
+    px = present(nx);
+    pz = present(nz);
   }
+  auto cleared = [&](int b, int kind) { return (cf == kind && b < g.first_n) || (cl == kind && b >= g.last_from); };
+  auto px_of = [&](int b) { return PAPER && cleared(b, 1) ? 0.0f : px; };
+  auto pz_of = [&](int b) { return PAPER && cleared(b, 2) ? 0.0f : pz; };
   const int kx = t * g.nstab + max(nx, 0), kz = t * g.nstab + max(nz, 0);
   const uint64_t mx = nx >= 0 ? 1ull << (kx & 63) : 0ull, mz = nz >= 0 ? 1ull << (kz & 63) : 0ull;
   // samples blockIdx.y + k gridDim.y, four per pass: their detector reads
@@ -95,13 +99,13 @@ __global__ void __launch_bounds__(256) unpack_kernel(Geom g, const int32_t* __re
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      unpack_store<FP32, PADDED, PAPER>(g, b + u * gy, v, t, s, (wx[u] & mx) != 0, (wz[u] & mz) != 0, px, pz,
-                                        out, by_h);
+      unpack_store<FP32, PADDED, PAPER>(g, b + u * gy, v, t, s, (wx[u] & mx) != 0, (wz[u] & mz) != 0,
+                                        px_of(b + u * gy), pz_of(b + u * gy), out, by_h);
   }
   for (; b < batch; b += gy) {
     const uint64_t* row = det + (long long)b * g.Wd;
-    unpack_store<FP32, PADDED, PAPER>(g, b, v, t, s, (row[kx >> 6] & mx) != 0, (row[kz >> 6] & mz) != 0, px,
-                                      pz, out, by_h);
+    unpack_store<FP32, PADDED, PAPER>(g, b, v, t, s, (row[kx >> 6] & mx) != 0, (row[kz >> 6] & mz) != 0,
+                                      px_of(b), pz_of(b), out, by_h);
   }
 }
 
