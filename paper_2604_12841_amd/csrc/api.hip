@@ -58,6 +58,7 @@ struct pd_predecoder {
   std::vector<pd_layer> layers;
   int ks = 3;                    // kernel size of the conv layers: 3, or 5 (Model 3 of Table models)
   Tiling tiling{};               // shared by every k x k x k layer (bf16 and fp8 paths)
+  Tiling sums{};                 // ... that the K parts of the sums are counted over (conv_parts, sum_plan)
   Tiling small[2]{};             // tiles of 64 and 128 voxels for the small-launch kernel (span 0: none)
   Workspace ws;                  // sized for max_batch
   int32_t* tables = nullptr;
@@ -291,7 +292,10 @@ Tiling plan_small(const Geom& g, int rows, int ks) {
   return best;
 }
 
-Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
+// boxes: with boxes of whole rounds instead of cells (a cell's rows run on
+// from tile to tile, a box's last rounds may be short): not a tiling that
+// runs, but the one that the K parts of the sums are counted over.
+Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3, bool boxes = false) {
   // 5x5x5 layers: their own (larger) staging buffers, cells on a halo of two
   const int kMaxSpan = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                : pd::conv_hidden_max_span(5);
@@ -333,7 +337,18 @@ Tiling plan_tiling(const Geom& g, int max_batch, int ks = 3) {
   // cells
   for (int BJ = 1; BJ <= g.H; ++BJ)
     for (int BI = 1; BI <= g.H; ++BI) {
-      const Tiling t = cell_tiling(g, BI, BJ, pd::kTileRows, kMaxSpan);
+      Tiling t{};
+      if (boxes) {
+        const int BT = std::min(g.T, pd::kTileRows / (BI * BJ)), halo = 2 * g.pad;
+        if (BT < 1) break;
+        t.mode = 1;
+        t.ntT = (g.T + BT - 1) / BT;
+        t.ntI = (g.H + BI - 1) / BI;
+        t.ntJ = (g.H + BJ - 1) / BJ;
+        t.span = (BT + halo) * (BI + halo) * (BJ + halo);
+      } else {
+        t = cell_tiling(g, BI, BJ, pd::kTileRows, kMaxSpan);
+      }
       // (a cell row of BJ < 16 voxels, whose 16-lane LDS reads span two
       // staged lines, costs little: at d = T = 25 a 5x3x16 box and a 9x13x2
       // box reached 0.54 and 0.53 of peak per MFMA row, so the row count
@@ -684,7 +699,8 @@ struct LayerRun {
 
 // ---- The K parts of a layer's sums (bf16).  A sum is taken as P = 2^k parts
 // of consecutive input-channel chunks, added in order.  P depends on the
-// layer and the launch's size only, never on the kernel that runs it, so a
+// layer and the launch's size only (counted in boxes of 256 voxels, see
+// plan_tiling), never on the kernel that runs it or how it is tiled, so a
 // handle's results for a batch size do not depend on how its launches are
 // shaped: few tiles (a small batch) take more parts, whose chains run side
 // by side, up to one unit (tile, output slice, part) per compute unit.  Of
@@ -881,7 +897,7 @@ struct SumPlan {
 SumPlan sum_plan(const pd_predecoder* h, const LayerRun& L, int batch) {
   const int nsl = L.cout / L.cw;
   auto tiles_of = [&](int nb) {
-    Tiling t = h->tiling;
+    Tiling t = h->sums;
     tiling_for_batch(&t, h->g, nb);
     return t.ntiles;
   };
@@ -891,7 +907,7 @@ SumPlan sum_plan(const pd_predecoder* h, const LayerRun& L, int batch) {
   if (p.parts == 1 && q >= 1 && q <= kMaxTailRounds && units % round != 0) {
     // the most first samples whose tiles fit q full rounds (tiles grow with
     // the batch: per sample, or one flat run of batch x V voxels)
-    const Tiling& base = h->tiling;
+    const Tiling& base = h->sums;
     const long long fit = q * round / nsl;  // tiles
     const bool flat = base.mode == 0 && (base.seg_len < 0 || base.tiles_per_seg == 0);
     const long long per = base.mode == 1 ? (long long)base.ntT * base.ntI * base.ntJ : base.tiles_per_seg;
@@ -1248,6 +1264,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
   h->cmax = cmax;
   if (dtype != PD_DTYPE_FP32) {
     h->tiling = plan_tiling(g, max_batch, ks);
+    h->sums = plan_tiling(g, max_batch, ks, true);
     for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, ks);
     const int max_span = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                  : pd::conv_hidden_max_span(5);
@@ -1485,6 +1502,7 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
     return PD_ERR_DEVICE;
   }
   h->tiling = plan_tiling(g, max_batch);
+  h->sums = plan_tiling(g, max_batch, 3, true);
   for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, 3);
   if (h->tiling.span <= 0 || h->tiling.span > pd::conv_hidden_max_span(3)) {
     delete h;
@@ -1876,7 +1894,7 @@ bool same_sums(const pd_layer* layers, int n, int dtype, int layout, int d, int 
     h[k].g = make_geom(d, Ts[k], layout, 0, 0, (h[k].ks - 1) / 2);
     h[k].dtype = dtype;
     h[k].n_cu = n_cu;
-    h[k].tiling = plan_tiling(h[k].g, Bs[k], h[k].ks);
+    h[k].sums = plan_tiling(h[k].g, Bs[k], h[k].ks, true);
   }
   for (int l = 1; l < n - 1; ++l) {
     LayerRun L{};
