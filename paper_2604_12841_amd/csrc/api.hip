@@ -59,7 +59,7 @@ struct pd_predecoder {
   int ks = 3;                    // kernel size of the conv layers: 3, or 5 (Model 3 of Table models)
   Tiling tiling{};               // shared by every k x k x k layer (bf16 and fp8 paths)
   Tiling sums{};                 // ... that the K parts of the sums are counted over (conv_parts, sum_plan)
-  Tiling small[2]{};             // tiles of 64 and 128 voxels for the small-launch kernel (span 0: none)
+  Tiling small[3]{};             // tiles of 64, 96 and 128 voxels for the small-launch kernel (span 0: none)
   Workspace ws;                  // sized for max_batch
   int32_t* tables = nullptr;
   std::vector<void*> wdev;       // per conv layer: fragments
@@ -760,11 +760,13 @@ struct SmallShape {
 constexpr SmallShape kSmallBf16[] = {
     {1, 64, 64, 16, 4.5, 3.7, 1.1}, {1, 128, 64, 32, 4.3, 7.3}, {1, 128, 128, 64, 6.0, 9.5},
     {2, 64, 32, 16, 3.9, 2.7},  {2, 64, 64, 32, 4.0, 5.0},  {2, 128, 64, 64, 4.5, 5.0},
+    {2, 96, 128, 96, 6.0, 7.2},
     {4, 64, 32, 32, 3.9, 1.65}, {4, 64, 64, 64, 3.6, 2.7},  {4, 128, 32, 64, 4.0, 3.0}};
 constexpr SmallShape kSmallFp8[] = {{4, 64, 32, 32, 4.5, 1.35}, {4, 64, 64, 64, 4.4, 2.35}, {4, 128, 64, 128, 5.4, 4.4}};
 constexpr SmallShape kSmall5[] = {
     {1, 64, 64, 16, 5.0, 14.5}, {1, 128, 64, 32, 5.0, 26.3}, {1, 128, 128, 64, 6.0, 43.0},
     {2, 64, 32, 16, 4.5, 9.7},  {2, 64, 64, 32, 5.0, 18.0},  {2, 128, 64, 64, 5.0, 22.0},
+    {2, 96, 128, 96, 6.0, 31.0},
     {4, 64, 32, 32, 4.5, 9.7},  {4, 64, 64, 64, 5.0, 17.0},  {4, 128, 32, 64, 5.0, 13.5}};
 
 double small_us(const pd_predecoder* h, const LayerRun& L, int batch, int parts, pd::SmallPlan* plan) {
@@ -773,8 +775,9 @@ double small_us(const pd_predecoder* h, const LayerRun& L, int batch, int parts,
   const int cout = L.epi == 2 ? 32 : L.cout;
   double best = 1e30;
   auto consider = [&](const SmallShape& s) {
-    const Tiling& t = h->small[s.rows == 128];
+    const Tiling& t = h->small[s.rows / 32 - 2];
     if (s.kg != kg || t.span == 0 || L.cw % s.cols != 0 || (parts > 4 && !fp8 && s.rows != 64)) return;
+    if (s.rows == 96 && row <= 128) return;  // (two 128 x 64 tiles share a CU there, which is no slower)
     // (a fused head needs all channels in the tile; wider ones take a kernel of their own)
     if (L.carries_head && cout == 64 && s.cols != 64) return;
     const long long units = (long long)batch * t.ntT * t.ntI * t.ntJ * (cout / s.cols);
@@ -860,7 +863,7 @@ pd::HiddenCall layer_call(const pd_predecoder* h, Workspace& ws, const Tiling& t
 pd_status run_small(const pd_predecoder* h, Workspace& ws, const LayerRun& L, const pd::SmallPlan& plan, float* logits,
                     int b0, int nb, hipStream_t st) {
   const bool fp8 = h->dtype == PD_DTYPE_FP8;
-  Tiling t = h->small[plan.rows == 128];
+  Tiling t = h->small[plan.rows / 32 - 2];
   tiling_for_batch(&t, h->g, nb);
   pd::HiddenCall c = layer_call(h, ws, t, L, logits, b0, nb, st);
   const bool head_after = L.epi == 1 && L.cout != 64;
@@ -1265,7 +1268,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
   if (dtype != PD_DTYPE_FP32) {
     h->tiling = plan_tiling(g, max_batch, ks);
     h->sums = plan_tiling(g, max_batch, ks, true);
-    for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, ks);
+    for (int k = 0; k < 3; ++k) h->small[k] = plan_small(g, 64 + 32 * k, ks);
     const int max_span = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                  : pd::conv_hidden_max_span(5);
     if (h->tiling.span <= 0 || h->tiling.span > max_span) {
@@ -1503,7 +1506,7 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
   }
   h->tiling = plan_tiling(g, max_batch);
   h->sums = plan_tiling(g, max_batch, 3, true);
-  for (int k = 0; k < 2; ++k) h->small[k] = plan_small(g, 64 << k, 3);
+  for (int k = 0; k < 3; ++k) h->small[k] = plan_small(g, 64 + 32 * k, 3);
   if (h->tiling.span <= 0 || h->tiling.span > pd::conv_hidden_max_span(3)) {
     delete h;
     return PD_ERR_UNSUPPORTED;

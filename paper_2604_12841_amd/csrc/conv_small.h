@@ -55,7 +55,8 @@ struct SmallArgs {
 // or 2, the 5x5x5 output layer; a head needs cols == c_out) on tiles of pl,
 // c.tl a mode 1 tiling of tiles of pl.rows voxels.  c.slice_width: output
 // channels of a slice of c.wfrag / c.bias.  Shapes: 1 part 64 x 64, 128 x 64,
-// 128 x 128; 2 parts 64 x 32, 64 x 64, 128 x 64; 4 parts 64 x 32, 64 x 64,
+// 128 x 128; 2 parts 64 x 32, 64 x 64, 128 x 64, 96 x 128 (rows of more than
+// 128 bytes); 4 parts 64 x 32, 64 x 64,
 // 128 x 32; more 64 x 32, 64 x 64; fp8 64 x 32, 64 x 64, 128 x 64.
 hipError_t launch_conv_small(const SmallPlan& pl, const HiddenCall& c, bool fp8);
 

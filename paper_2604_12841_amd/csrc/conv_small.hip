@@ -3,8 +3,8 @@
 // points and epilogues) when its 256-voxel tiles would leave the chip mostly
 // idle.  There a layer's time is one workgroup's chain of latencies, not
 // matrix work, so this kernel shortens that chain:
-//   * A workgroup (4 waves) computes a tile of 64 or 128 voxels x 32 to 128
-//     output channels.  Its waves are KG K groups x WM voxel groups x WN
+//   * A workgroup (4 waves) computes a tile of 64, 96 or 128 voxels x 32
+//     to 128 output channels.  Its waves are KG K groups x WM voxel groups x WN
 //     channel groups; a wave owns MB x NB blocks of 32 voxels x 32 channels
 //     and the consecutive input-channel chunks (32 bytes per voxel) of its K
 //     group.  The partial sums meet in LDS, where every lane finishes 8
@@ -33,6 +33,11 @@
 // / 15.9 / 16.5 -> 5.6 / 11.7 / 11.6, 128 channels bf16 18.5 / 30.0 / 33.0 ->
 // 7.4 / 23.8 / 27.1, 128 channels fp8 15.4 / 21.9 / 22.1 -> 5.8 / 16.2 / 19.1;
 // a 5x5x5 layer at d = 13 / 21 42.9 / 66.6 -> 24.6 / 62.5.
+// Two parts take 96 x 128 tiles (six MFMAs for 2 KB of weights and 3 of
+// fragments; 128 x 64 ones four for 2 and 2) where 128 x 64 ones are a few more
+// than the CUs: Model 3 at d = 13, batch 8 (its 128-wide 5x5x5 layers, 184
+// tiles instead of 288) 250 -> 207 us, Model 6 at 13^3, batch 16 (the last two
+// samples of the 512-wide layers) 2740 -> 2545.
 #include <algorithm>
 
 #include "activation.h"
@@ -496,7 +501,8 @@ hipError_t launch_bf16(const SmallArgs& a, long long n, const SmallPlan& pl, int
          try_shape<KS, false, false, ONE, 4, false, 1, 1, 4, 1>(a, n, pl, epi, st, &e));
   if constexpr (!ONE) {
     if (e == hipErrorInvalidValue)
-      (void)(try_shape<KS, false, false, ONE, 4, true, 1, 1, 2, 1>(a, n, pl, epi, st, &e) ||
+      (void)(try_shape<KS, false, false, ONE, 2, false, 1, 2, 3, 2>(a, n, pl, epi, st, &e) ||
+             try_shape<KS, false, false, ONE, 4, true, 1, 1, 2, 1>(a, n, pl, epi, st, &e) ||
              try_shape<KS, false, false, ONE, 4, true, 1, 1, 2, 2>(a, n, pl, epi, st, &e));
   }
   return e;

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import paper_2604_12841_amd as pdx
+import test_gpu_model6 as resnets
 import tight
 from paper_2604_12841_amd import workload
 from parity import dev_u64, say
@@ -68,6 +69,10 @@ CASES = [
     ("paper", [64, 64, 64], 5, 5, 4, 1, "bf16"),            # 5x5x5, one piece
     ("paper", [128, 128, 128], 5, 9, 9, 1, "bf16"),         # ... eight parts
     ("paper", [128, 128], 5, 13, 6, 3, "bf16"),
+    # 96-voxel tiles of two parts
+    ("paper", [128, 128, 128], 5, 13, 13, 8, "bf16"),
+    ("paper", [128, 128], 5, 9, 7, 24, "bf16"),
+    ("paper", [128, 256, 128], 3, 17, 17, 4, "bf16"),
     # the persistent kernel on cells
     ("plaquette", [64, 64], 3, 19, 19, 70, "bf16"),
     ("plaquette", [128, 128], 3, 21, 5, 200, "bf16"),
@@ -126,3 +131,9 @@ def test_layers_tight(cuda, layout, widths, k, d, T, B, dtype):
     assert bool((err <= eps).all())
     assert bool(torch.isfinite(logits).all())
     pre.close()
+
+
+def test_resnet_96_voxel_tiles(cuda):
+    """Two-part layers with a shortcut (its row, or its projection) in the epilogue."""
+    resnets.test_resnet_convs_tight(cuda, dict(name="w128_two_parts", blocks=workload.resnet_blocks([128, 128]), d=9,
+                                               T=9, B=24, layout="paper"))
