@@ -746,7 +746,10 @@ int conv_parts(const pd_predecoder* h, const LayerRun& L, long long tiles) {
 // at batches 1 to 8 to about 15 %; at the line the two are as close
 // (small / persistent, 128 channels: bf16 45 / 48 us at 41k voxels, 76 / 78 at
 // 81k, 100 / 94 at 127k; fp8 42 / 50 at 81k, 62 / 56 at 127k; at 32k voxels
-// 27 / 48, fp8 19 / 32).
+// 27 / 48, fp8 19 / 32).  Past a full round of the persistent kernel's units it
+// always runs: small launches then cost 4 to 28 % more (networks of four layers
+// at 617 units: 128 channels bf16 510 / 426 us, fp8 311 / 260; 64 channels at 615
+// 166 / 159, at 3600 817 / 706), all but the first few units over.
 
 // Small launches: a workgroup costs `fixed` (start, staging, the sums'
 // exchange, epilogue) and `piece` per 128-byte piece of its input rows; where
@@ -819,11 +822,9 @@ BigTime big_time(const pd_predecoder* h, const LayerRun& L) {
   return {1.75 * m + (L.cw == 64 ? 8.0 : 3.0), 3.3 * m + 12.0, 2ll * h->n_cu};
 }
 
-double big_us(const BigTime& b, long long units) {
-  const long long q = units / b.round, r = units % b.round;
+double big_us(const BigTime& b, long long units) {  // units <= b.round
   const double half = b.round / 2.0;
-  const double rest = r == 0 ? 0.0 : (r <= half ? b.t1 : b.t1 + (b.t2 - b.t1) * (0.5 + 0.5 * (r - half) / half));
-  return q * b.t2 + rest;
+  return units <= half ? b.t1 : b.t1 + (b.t2 - b.t1) * (0.5 + 0.5 * (units - half) / half);
 }
 
 // Launches of samples b0 .. b0 + nb - 1 (every per-sample pointer moved on).
@@ -941,7 +942,8 @@ pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, f
     const double small = small_us(h, L, nb, parts, &plan);
     Tiling t = h->tiling;
     tiling_for_batch(&t, h->g, nb);
-    if (parts > 1 || b0 > 0 || small * 1.05 < big_us(bt, t.ntiles * (L.cout / L.cw)))
+    const long long units = t.ntiles * (L.cout / L.cw);
+    if (parts > 1 || b0 > 0 || (units <= bt.round && small * 1.05 < big_us(bt, units)))
       return run_small(h, ws, L, plan, logits, b0, nb, st);
     return run_big(h, ws, L, logits, nb, st);
   };
