@@ -30,7 +30,7 @@
 //     (3 v + g) mod 16, so 16 consecutive staged voxels hit 16 distinct
 //     groups, and a fragment read of 32 consecutive staged voxels (flat
 //     tiles) or the staging stores meet no group twice in one LDS cycle
-//     (measured).  A read whose 32 voxels come from two rows of a box, with
+//     (measured).  A read whose 32 voxels come from two rows of a cell, with
 //     the rows' halo voxels between them, costs a few cycles more, which the
 //     LDS pipe absorbs (it is less than half busy here).  Flat tiles stage
 //     only the real columns; reads of the left / right halo column are
@@ -82,7 +82,7 @@ constexpr int VSTRIDE = 48;   // LDS bytes per staged voxel (32 of channels + 16
 // and the workgroups per CU.  KS = 3: two workgroups per CU, so each SIMD
 // runs one wave of each and one workgroup's epilogue, barriers and staging
 // stalls overlap the other's matrix work.  KS = 5: a 256-voxel tile's halo
-// of two makes its footprint about 4.5 times the tile (a 4 x 8 x 8 box
+// of two makes its footprint about 4.5 times the tile (a 4 x 8 x 8 one
 // stages 8 x 12 x 12 voxels), so one workgroup per CU with larger staging
 // buffers; its 125-step chunks keep the matrix pipe busy between barriers.
 template <int KS>
@@ -250,6 +250,10 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
                    float* __restrict__ logits, int batch, const uint16_t* __restrict__ sc, int sc_stride, int lsl, uint32_t* __restrict__ sched,
                    int nstat) {
   static_assert(KS == 3 || MODE == 1, "5x5x5 layers run on cell tiles");
+  // One tiling's index arithmetic per instance: without the other's, half the
+  // scalar registers spilled here stay in place (64-channel fp8 layers at d = 9,
+  // batch 110: 74.6 -> 73.0 us a network of four).
+  __builtin_assume(tl.mode == MODE);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using W = Split<COUT>;
   using L = Lds<COUT, KS>;
@@ -486,7 +490,7 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   // read by every wave at the top of iteration it + 1 (a chunk's barrier in
   // between).  Counters sit in separate 64-byte lines (grab, then done, per
   // XCD); the last workgroup of an XCD to finish puts both back to zero for
-  // the next launch.  Box tiles fix two units (c5: about 3 % less time);
+  // the next launch.  Cells fix two units (c5: about 3 % less time);
   // flat tiles fix seven eighths of a workgroup's share: fixed shares keep
   // an XCD's workgroups on neighbouring tiles' chunks together, whose lines
   // L2 then serves to all of them, and counters from the third unit on
