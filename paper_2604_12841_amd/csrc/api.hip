@@ -1404,7 +1404,9 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
       }
       s = upload(&wd, f.data(), f.size() * 2);
     } else {
-      std::vector<float> r = pd::conv_fp32_fragments(w, L.c_in, L.c_out);
+      const int head = i == n_layers - 2;
+      std::vector<float> r = pd::conv_fp32_fragments(w, L.c_in, L.c_out, head);
+      bias_dev = pd::conv_fp32_bias(b, L.c_out, head);
       s = upload(&wd, r.data(), r.size() * 4);
     }
     h->wdev.push_back(wd);

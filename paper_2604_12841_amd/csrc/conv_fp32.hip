@@ -1,21 +1,28 @@
 // conv_fp32.hip -- one 3x3x3 conv3d layer in fp32 end to end (Sec. IV.B, Fig.
 // ConvArch; stride 1, zero padding, cross-correlation) as an implicit GEMM on
-// the fp32 matrix cores, v_mfma_f32_16x16x4_f32 (fp32 operands and sums: an
-// fma chain per output in another order than a scalar loop), with bias and
-// activation fused in, and for the last hidden layer the 1x1x1 head and the
-// threshold.  Same zero-halo NTHWC layout as the bf16 path, so every tap is
-// an index shift and the K loop has no bounds checks.
+// the fp32 matrix cores, v_mfma_f32_16x16x4_f32, with bias and activation
+// fused in, and for the last hidden layer the 1x1x1 head and the threshold.
+// Same zero-halo NTHWC layout as the bf16 path, so every tap is an index
+// shift and the K loop has no bounds checks.
 //
 //   out[co][m] = act(bias[co] + sum_{tap, ci} W[co][ci][tap] * X[m + shift(tap)][ci])
 //
+// Order of the sums: one fma chain per output, from the bias over the taps
+// and, within a tap, the input channels in order; a logit from the head's bias
+// over its channels in order.  The instruction is a chain of four fmas in k
+// order (bit for bit on 4 M random outputs, subnormal ones among them), so
+// results are a scalar loop's, whatever the tiles and the batch, and a logit
+// near zero keeps its sign.
+//
 // Rows are output channels (A, weights), columns output voxels (B).  Lane l
-// of an operand holds k = l / 16 of a k-step of 4; which input channel that
-// is, is free as long as both operands agree, so a lane reads the 4
-// consecutive channels 4 (l / 16) .. + 3 of a 16-channel chunk with one
-// 16-byte load and feeds one of them to each of four k-steps.  Weights are
-// stored in that order at create (conv_fp32_fragments).  (c_in an odd multiple
-// of 8: chunks of 8 channels, 8-byte loads, two k-steps.)  Layer 1 (c_in = 2):
-// lane l takes tap 4 m + l / 16, both channels, two k-steps per m.
+// of an operand holds k = l / 16 of a k-step of 4, so k-step s of a 16-channel
+// chunk needs channel 4 s + l / 16 there.  For a lane to read its channels of
+// four k-steps with one 16-byte load, a voxel's row is stored with channel 4 s
+// + g of a chunk in place 4 g + s (stored_channel); the layer before writes
+// that order by taking its own weight rows and biases in it.  (c_in an odd
+// multiple of 8: chunks of 8 channels, 8-byte loads, two k-steps, channel 4 s
+// + g in place 2 g + s.)  Layer 1 (c_in = 2): k runs over (tap, channel), a
+// k-step takes two taps.
 //
 // Work split: a wave owns MB blocks of 16 consecutive interior voxels x NB
 // blocks of 16 output channels and shares nothing with other waves: no LDS,
@@ -71,7 +78,7 @@ __device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgc
 
 // FIRST: c_in = 2, per-lane taps.  HEAD: the wave holds every channel of its
 // voxels (NB blocks cover c_out) and writes the head's logits and nibbles
-// instead of y.
+// instead of y.  bias: of the rows in order (conv_fp32_bias).
 // C8: chunks of 8 input channels instead of 16 (c_in an odd multiple of 8).
 template <int MB, int NB, int DEPTH, bool FIRST, bool C8, bool HEAD>
 __global__ void __launch_bounds__(64 * MAX_WAVES)
@@ -117,21 +124,28 @@ __global__ void __launch_bounds__(64 * MAX_WAVES)
   const int nbt = (cout + 15) >> 4;  // channel blocks of the layer
   f32x4 acc[MB][NB];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int nb = 0; nb < NB; ++nb) {  // lane: rows 4 grp .. + 3 of the block (past the last block: no rows)
+    const int row = (cg * NB + nb) * 16 + grp * 4;
+    const f32x4 b0 = row < nbt * 16 ? *reinterpret_cast<const f32x4*>(bias + row) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int mb = 0; mb < MB; ++mb) acc[mb][nb] = b0;
+  }
 
   if constexpr (FIRST) {
-    // k-steps (m, channel): fragment m holds lane l's two weights of tap 4 m + l / 16 as its first two words
+    // fragment m: lane l's weights of two k-steps, 2 m and 2 m + 1; a k-step s is taps 2 s and 2 s + 1 (lane l: tap
+    // 2 s + l / 32, channel (l / 16) % 2)
 #pragma unroll
     for (int m = 0; m < 7; ++m) {
-      const int tap = 4 * m + grp;
-      const int tc = tap < 27 ? tap : 0;  // the tap past the last has zero weights
-      const int dt = tc / 9, di = (tc / 3) % 3, dj = tc % 3;
-      const uint32_t to = (uint32_t)((dt * g.P + di * g.Wp + dj) * 2) * 4u;
-      u32x2 bv[MB], av[NB];
+      u32x2 av[NB];
+      uint32_t bv[MB][2];
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) bv[mb] = __builtin_amdgcn_raw_buffer_load_b64(xr, voff[mb] + to, 0, 0);
+      for (int s = 0; s < 2; ++s) {
+        const int t0 = 4 * m + 2 * s, t1 = t0 < 26 ? t0 + 1 : t0;  // the tap past the last: weights of -0, which add nothing
+        const int o0 = (t0 / 9) * g.P + (t0 / 3) % 3 * g.Wp + t0 % 3, o1 = (t1 / 9) * g.P + (t1 / 3) % 3 * g.Wp + t1 % 3;
+        const uint32_t to = (uint32_t)((grp >> 1 ? o1 : o0) * 2 + (grp & 1)) * 4u;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) bv[mb][s] = __builtin_amdgcn_raw_buffer_load_b32(xr, voff[mb] + to, 0, 0);
+      }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
         av[nb] = __builtin_amdgcn_raw_buffer_load_b64(wr, lane * 8u, (uint32_t)((m * nbt + cg * NB + nb) * 512), 0);
@@ -196,39 +210,39 @@ __global__ void __launch_bounds__(64 * MAX_WAVES)
     }
   }
 
-  // Lane holds channels co .. co + 3 (co = 16 (cg NB + nb) + 4 grp) of voxel
-  // u0 + 16 mb + l16.
+  // Lane holds rows 16 (cg NB + nb) + 4 grp .. + 3, in that place of voxel u0 + 16 mb + l16.
   if constexpr (HEAD) {
+    // Value e of a lane is channel 16 nb + 4 e + grp (conv_fp32_fragments): the
+    // B operand of the head's k-step of channels 16 nb + 4 e .. + 3.  Rows 0..3
+    // of A are the head's filters.
+    f32x4 lg[MB];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      float lg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int co = nb * 16 + grp * 4;
-        if (co < cout) {
+      for (int o = 0; o < 4; ++o) lg[mb][o] = grp == 0 ? head_b[o] : 0.0f;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float a = activation_f32(acc[mb][nb][e] + bias[co + e], act);
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int o = 0; o < 4; ++o) lg[o] = fmaf(head_w[o * cout + co + e], a, lg[o]);
-          }
+      for (int e = 0; e < 4; ++e) {
+        const int c = nb * 16 + e * 4;
+        if (c < cout) {  // uniform
+          const float hw = l16 < 4 ? head_w[l16 * cout + c + grp] : 0.0f;
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+            lg[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(hw, activation_f32(acc[mb][nb][e], act), lg[mb], 0, 0, 0);
         }
       }
-      // the lanes l16 + 16 k hold the voxel's other channels
 #pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        lg[o] += __shfl_xor(lg[o], 16);
-        lg[o] += __shfl_xor(lg[o], 32);
-        lg[o] += head_b[o];
-      }
+    for (int mb = 0; mb < MB; ++mb) {
       const int u = u0 + 16 * mb + l16;
       if (u < nvox && grp == 0) {
         int b, t, i, j;
         coords(u, b, t, i, j);
-        nib[u] = (uint8_t)flip_nibble(g, tables, i, j, lg);
+        const float l4[4] = {lg[mb][0], lg[mb][1], lg[mb][2], lg[mb][3]};
+        nib[u] = (uint8_t)flip_nibble(g, tables, i, j, l4);
         if (logits) {
 #pragma unroll
-          for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + i * g.H + j] = lg[o];
+          for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + i * g.H + j] = l4[o];
         }
       }
     }
@@ -237,12 +251,11 @@ __global__ void __launch_bounds__(64 * MAX_WAVES)
     for (int nb = 0; nb < NB; ++nb) {
       const int co = (cg * NB + nb) * 16 + grp * 4;
       if (co < cout) {
-        const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + co);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
           f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = activation_f32(acc[mb][nb][e] + bv[e], act);
+          for (int e = 0; e < 4; ++e) v[e] = activation_f32(acc[mb][nb][e], act);
           if (u0 + 16 * mb + l16 < nvox) *reinterpret_cast<f32x4*>(y + (long long)pv[mb] * cout + co) = v;
         }
       }
@@ -250,29 +263,54 @@ __global__ void __launch_bounds__(64 * MAX_WAVES)
   }
 }
 
+// k-steps of a chunk of a c-channel row (c a multiple of 8).
+inline int chunk_steps(int c) { return c % 16 ? 2 : 4; }
+
+// Channel in place p of a row stored in chunks of n k-steps: channel 4 s + g of a chunk lies in place n g + s.
+inline int stored_channel(int p, int n) {
+  const int q = p % (4 * n);
+  return p - q + 4 * (q % n) + q / n;
+}
+
+// Output channel of weight row r: the place it is stored in, by the chunks
+// of the next layer; a head's layer stores nothing and takes chunks of 16.
+inline int row_channel(int r, int cout, int head) { return stored_channel(r, head ? 4 : chunk_steps(cout)); }
+
 }  // namespace
 
-// Fragments of an fp32 layer: [iteration][channel block of 16][64 lanes][n]
-// floats, iterations (tap, chunk of 4 n input channels), n = 4, or 2 when c_in
-// is an odd multiple of 8: lane l holds channels 4 n chunk + n (l / 16) + e
-// of output channel 16 block + l % 16.  c_in = 2: 7 iterations, n = 2, lane l
-// holding both channels of tap 4 iteration + l / 16.  What does not exist is
-// zero.
-std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout) {
-  const int nbt = (cout + 15) / 16, n = cin % 16 ? 2 : 4;
+// Fragments of an fp32 layer: [iteration][block of 16 rows][64 lanes][n]
+// floats, iterations (tap, chunk of 4 n input channels), n = chunk_steps:
+// lane l holds channels 4 n chunk + 4 s + l / 16, s = 0 .. n - 1, of row 16
+// block + l % 16.  c_in = 2: 7 iterations, n = 2, over k = 2 tap + channel:
+// lane l holds k = 8 iteration + 4 s + l / 16 (past the last tap -0: the
+// events are 0 or 1, and a sum plus -0 is the sum).  Rows that do not exist
+// are zero.
+std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout, int head) {
+  const int nbt = (cout + 15) / 16, n = cin == 2 ? 2 : chunk_steps(cin);
   const int nch = cin / (4 * n), niter = cin == 2 ? 7 : 27 * nch;
   std::vector<float> f((size_t)niter * nbt * 64 * n, 0.0f);
   for (int it = 0; it < niter; ++it)
     for (int nb = 0; nb < nbt; ++nb)
       for (int l = 0; l < 64; ++l) {
-        const int co = nb * 16 + l % 16, gr = l / 16;
-        const int tap = cin == 2 ? 4 * it + gr : it / nch;
-        const int c0 = cin == 2 ? 0 : (it % nch) * 4 * n + n * gr;
-        if (co >= cout || tap >= 27) continue;
-        for (int e = 0; e < n; ++e)
-          f[(((size_t)it * nbt + nb) * 64 + l) * n + e] = w[((size_t)co * cin + c0 + e) * 27 + tap];
+        const int co = row_channel(nb * 16 + l % 16, cout, head);
+        if (co >= cout) continue;
+        for (int s = 0; s < n; ++s) {
+          const int k = 8 * it + 4 * s + l / 16;
+          const int tap = cin == 2 ? k / 2 : it / nch, ci = cin == 2 ? k % 2 : (it % nch) * 4 * n + 4 * s + l / 16;
+          f[(((size_t)it * nbt + nb) * 64 + l) * n + s] = tap < 27 ? w[((size_t)co * cin + ci) * 27 + tap] : -0.0f;
+        }
       }
   return f;
+}
+
+// Biases of the rows of an fp32 layer, in whole blocks of 16.
+std::vector<float> conv_fp32_bias(const float* b, int cout, int head) {
+  std::vector<float> r((size_t)(cout + 15) / 16 * 16, 0.0f);
+  for (size_t k = 0; k < r.size(); ++k) {
+    const int co = row_channel((int)k, cout, head);
+    if (co < cout) r[k] = b[co];
+  }
+  return r;
 }
 
 hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const float* x, float* y, const float* w,

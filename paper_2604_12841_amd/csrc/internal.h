@@ -252,14 +252,17 @@ __host__ __device__ inline long long conv_workgroups(long long ntiles, long long
 
 // A 3x3x3 layer in fp32: c_in = 2 or a multiple of 8 up to 128, c_out a
 // multiple of 8 up to 128, x and y rows of c_in / c_out floats in the
-// zero-halo layout (pad 1), w the fragments of conv_fp32_fragments.  head:
-// the last hidden layer, whose epilogue applies the 1x1x1 head (head_w
-// [4][c_out]) and the threshold instead of writing y.
+// zero-halo layout (pad 1; within a row, channels in the order that the next
+// layer's loads want, see conv_fp32.hip), w and bias as conv_fp32_fragments
+// and conv_fp32_bias arrange them.  head: the last hidden layer, whose
+// epilogue applies the 1x1x1 head (head_w [4][c_out]) and the threshold
+// instead of writing y.
 hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const float* x, float* y, const float* w,
                             const float* bias, int head, const float* head_w, const float* head_b,
                             const int32_t* tables, uint8_t* nib, float* logits, int batch, int n_cu,
                             hipStream_t stream);
-std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout);
+std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout, int head);
+std::vector<float> conv_fp32_bias(const float* b, int cout, int head);
 
 // The 1x1x1 head and the threshold over activation rows of c_in (64 or 128)
 // values, bf16 or E4M3.
