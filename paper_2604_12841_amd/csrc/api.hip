@@ -686,10 +686,10 @@ struct StopAt {
 // applies it (epi 1) -- a run that stops at it must sum as the head's run does.
 struct LayerRun {
   int cin, cout, cw, act;
-  const void* x;
-  void* y;
-  const void* wfrag;
-  const float* bias;
+  const void* x = nullptr;
+  void* y = nullptr;
+  const void* wfrag = nullptr;
+  const float* bias = nullptr;
   int epi = 0;
   const float *head_w = nullptr, *head_b = nullptr;
   bool carries_head = false;
@@ -898,6 +898,31 @@ struct SumPlan {
   int parts, first, tail_parts;
 };
 
+// The tilings of a handle's launches of up to max_batch samples (h->g, h->ks).
+void plan_tilings(pd_predecoder* h, int max_batch) {
+  h->tiling = plan_tiling(h->g, max_batch, h->ks);
+  h->sums = plan_tiling(h->g, max_batch, h->ks, true);
+  for (int k = 0; k < 3; ++k) h->small[k] = plan_small(h->g, 64 + 32 * k, h->ks);
+}
+
+// Layer l >= 1 of a plain network, but for its buffers: a hidden one, or the
+// 5x5x5 output layer.
+LayerRun plain_layer(const pd_layer* layers, int n, int l) {
+  const pd_layer& a = layers[l];
+  LayerRun L{a.c_in, a.c_out, l == n - 1 ? 32 : std::min(a.c_out, 128), a.act};
+  L.epi = l == n - 1 ? 2 : 0;
+  L.carries_head = l == n - 2 && layers[n - 1].k == 1;
+  return L;
+}
+
+// conv1 or conv2 (second) of a residual block, but for its buffers.
+LayerRun block_conv(const pd_block& B, bool second) {
+  const int ci = second ? B.c_mid : B.c_in, co = second ? B.c_out : B.c_mid;
+  LayerRun L{ci, co, std::min(co, 128), B.act};
+  L.epi = second ? 4 : 0;
+  return L;
+}
+
 SumPlan sum_plan(const pd_predecoder* h, const LayerRun& L, int batch) {
   const int nsl = L.cout / L.cw;
   auto tiles_of = [&](int nb) {
@@ -928,28 +953,57 @@ SumPlan sum_plan(const pd_predecoder* h, const LayerRun& L, int batch) {
   return p;
 }
 
-// One hidden layer over the batch.
-pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, float* logits, int batch,
-                     hipStream_t st) {
-  pd::SmallPlan plan{};
+// A launch of a hidden layer: samples b0 .. b0 + nb - 1, their sums in `parts`
+// parts, on the small-launch kernel or the persistent one.
+struct Launch {
+  int b0, nb, parts;
+  bool small;
+  pd::SmallPlan plan;
+};
+
+// The launches of one hidden layer over a batch: one, or two.
+int layer_launches(const pd_predecoder* h, const LayerRun& L, int batch, Launch (&out)[2]) {
   if (L.epi == 2) {  // the 5x5x5 output layer: 4 filters on one block of 32
-    (void)small_us(h, L, batch, 4, &plan);
-    return run_small(h, ws, L, plan, logits, 0, batch, st);
+    out[0] = {0, batch, 4, true, {}};
+    (void)small_us(h, L, batch, 4, &out[0].plan);
+    return 1;
   }
   const BigTime bt = big_time(h, L);
-  // samples b0 .. b0 + nb - 1 with sums of `parts` parts
-  auto run = [&](int b0, int nb, int parts) {
-    const double small = small_us(h, L, nb, parts, &plan);
+  auto launch = [&](int b0, int nb, int parts) {
+    Launch r{b0, nb, parts, true, {}};
+    const double small = small_us(h, L, nb, parts, &r.plan);
     Tiling t = h->tiling;
     tiling_for_batch(&t, h->g, nb);
     const long long units = t.ntiles * (L.cout / L.cw);
-    if (parts > 1 || b0 > 0 || (units <= bt.round && small * 1.05 < big_us(bt, units)))
-      return run_small(h, ws, L, plan, logits, b0, nb, st);
-    return run_big(h, ws, L, logits, nb, st);
+    r.small = parts > 1 || b0 > 0 || (units <= bt.round && small * 1.05 < big_us(bt, units));
+    return r;
   };
   const SumPlan sp = sum_plan(h, L, batch);
-  const pd_status s = run(0, sp.first, sp.parts);
-  return s != PD_OK || sp.first == batch ? s : run(sp.first, batch - sp.first, sp.tail_parts);
+  out[0] = launch(0, sp.first, sp.parts);
+  if (sp.first == batch) return 1;
+  out[1] = launch(sp.first, batch - sp.first, sp.tail_parts);
+  return 2;
+}
+
+// One hidden layer over the batch.
+pd_status run_hidden(const pd_predecoder* h, Workspace& ws, const LayerRun& L, float* logits, int batch,
+                     hipStream_t st) {
+  Launch r[2];
+  const int n = layer_launches(h, L, batch, r);
+  pd_status s = PD_OK;
+  for (int k = 0; k < n && s == PD_OK; ++k)
+    s = r[k].small ? run_small(h, ws, L, r[k].plan, logits, r[k].b0, r[k].nb, st)
+                   : run_big(h, ws, L, logits, r[k].nb, st);
+  return s;
+}
+
+// Workgroups and whether units come from counters, of a layer's launch on the persistent kernel.
+bool big_counts(const pd_predecoder* h, const LayerRun& L, int nb) {
+  Tiling t = h->tiling;
+  tiling_for_batch(&t, h->g, nb);
+  const long long units = t.ntiles * (L.cout / L.cw);
+  return pd::conv_hidden_counts(
+      units, pd::conv_workgroups(units, (long long)h->n_cu * pd::conv_hidden_workgroups_per_cu(h->ks)));
 }
 
 // The path of a residual network (Model 6, Sec. VI, Fig. Model8Representation):
@@ -1003,7 +1057,11 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
         s = check_launch(pd::launch_conv_first(g, B.c_in, cw, nsl, h->wslice[2 * k], B.act, x, nullptr, hb, B.c_mid,
                                                h->wdev[2 * k], h->bdev[2 * k], batch, fp8, 3, st));
       } else {
-        LayerRun L{B.c_in, B.c_mid, cw, B.act, x, hb, h->wdev[2 * k], h->bdev[2 * k]};
+        LayerRun L = block_conv(B, false);
+        L.x = x;
+        L.y = hb;
+        L.wfrag = h->wdev[2 * k];
+        L.bias = h->bdev[2 * k];
         s = run_hidden(h, ws, L, nullptr, batch, st);
       }
       if (s != PD_OK) return s;
@@ -1044,8 +1102,13 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
                                            ws.nib, logits, batch, h->n_cu, fp8, sc, sc_stride, nullptr, nullptr,
                                            nullptr, st));
     } else {  // slices as for conv1, each also with its shortcut channels (or projection rows)
-      LayerRun L{B.c_mid, B.c_out, std::min(B.c_out, 128), B.act, hb, yb, h->wdev[2 * k + 1], h->bdev[2 * k + 1], 4,
-                 pw, pb};
+      LayerRun L = block_conv(B, true);
+      L.x = hb;
+      L.y = yb;
+      L.wfrag = h->wdev[2 * k + 1];
+      L.bias = h->bdev[2 * k + 1];
+      L.head_w = pw;
+      L.head_b = pb;
       L.sc = sc;
       L.sc_stride = sc_stride;
       s = run_hidden(h, ws, L, nullptr, batch, st);
@@ -1102,8 +1165,7 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
     const pd_layer& L = h->layers[l];
     const int row_bytes = L.c_out * (fp32 ? 4 : aelem);
     if ((s = prepare_rows(ws, l & 1, row_bytes, st)) != PD_OK) return s;
-    const bool head_layer = !out3 && l == n - 2;  // carries the head unless the run stops at it
-    const bool fuse_head = head_layer && stop < 0;
+    const bool fuse_head = !out3 && l == n - 2 && stop < 0;  // (a run that stops at the layer does not carry the head)
     if (fp32) {
       s = check_launch(pd::launch_conv_fp32(g, L.c_in, L.c_out, L.act, (const float*)x, (float*)y,
                                             (const float*)h->wdev[l], h->bdev[l], fuse_head ? 1 : 0, h->head_w,
@@ -1122,8 +1184,14 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
         s = check_launch(pd::launch_conv_first(g, L.c_in, cw, nsl, h->wslice[l], L.act, x, fused ? &pe : nullptr, y,
                                                L.c_out, h->wdev[l], h->bdev[l], batch, fp8, ks, st));
       } else {  // the last hidden layer may carry the head and the threshold in its epilogue
-        LayerRun R{L.c_in, L.c_out, cw, L.act, x, y, h->wdev[l], h->bdev[l], fuse_head ? 1 : 0, h->head_w, h->head_b,
-                   head_layer};
+        LayerRun R = plain_layer(h->layers.data(), n, l);
+        R.x = x;
+        R.y = y;
+        R.wfrag = h->wdev[l];
+        R.bias = h->bdev[l];
+        R.epi = fuse_head ? 1 : 0;
+        R.head_w = h->head_w;
+        R.head_b = h->head_b;
         s = run_hidden(h, ws, R, logits, batch, st);
       }
       head_done = fuse_head && l > 0;
@@ -1144,8 +1212,10 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
     s = check_launch(pd::launch_conv_out(g, L.c_in, x, h->wdev[n - 1], h->bdev[n - 1], h->tables, ws.nib, logits,
                                          batch, h->n_cu, fp8, nullptr, 0, nullptr, nullptr, nullptr, st));
   } else if (out3) {
-    const pd_layer& L = h->layers[n - 1];
-    LayerRun R{L.c_in, L.c_out, 32, L.act, x, nullptr, h->wdev[n - 1], h->bdev[n - 1], 2};
+    LayerRun R = plain_layer(h->layers.data(), n, n - 1);
+    R.x = x;
+    R.wfrag = h->wdev[n - 1];
+    R.bias = h->bdev[n - 1];
     s = run_hidden(h, ws, R, logits, batch, st);
   } else if (!head_done) {  // a one-hidden-layer network on the paper's layout
     s = check_launch(pd::launch_head(g, h->layers[n - 1].c_in, x, 0, h->head_w, h->head_b, h->tables, ws.nib, logits,
@@ -1171,6 +1241,60 @@ int n_stop_points(const pd_predecoder* h) {
 }  // namespace
 
 extern "C" {
+
+// For the tests: the launches that a network's layers (blocks given: a
+// residual network's convs) after the first take at `batch` samples on a
+// handle for max_batch, planned without a device for one of n_cu compute
+// units.  out: per launch 6 numbers -- the layer (conv1 and conv2 of block k:
+// 2 k and 2 k + 1), its samples, the tile's voxels (256: the persistent
+// kernel) and channels, the K parts of its sums, whether units come from
+// counters; fp32: a wave's voxels and channels.  Returns the launches, -1 for
+// a network that is not supported.
+int32_t pd_plan_launches(const pd_layer* layers, int32_t n_layers, const pd_block* blocks, int32_t n_blocks, int32_t d,
+                         int32_t T, int32_t dtype, int32_t layout, int32_t batch, int32_t max_batch, int32_t n_cu,
+                         int32_t* out, int32_t capacity) {
+  pd_predecoder h;
+  h.dtype = dtype;
+  h.n_cu = n_cu;
+  h.ks = blocks ? 3 : network_ks(layers);
+  h.g = make_geom(d, T, layout, 0, 0, (h.ks - 1) / 2);
+  if (!blocks && !supported(h.g, layers, n_layers, dtype)) return -1;
+  if (blocks) h.blocks.assign(blocks, blocks + n_blocks);
+  int n = 0;
+  auto put = [&](int l, int nb, int rows, int cols, int parts, int counts) {
+    if (n < capacity) {
+      const int32_t row[6] = {l, nb, rows, cols, parts, counts};
+      std::memcpy(out + 6 * n, row, sizeof row);
+    }
+    ++n;
+  };
+  if (dtype == PD_DTYPE_FP32) {
+    for (int l = 0; l < n_layers - 1; ++l) {
+      const pd::Fp32Blocks b =
+          pd::conv_fp32_blocks((long long)batch * h.g.V, layers[l].c_out, l == n_layers - 2, n_cu);
+      put(l, batch, 16 * b.mb, 16 * b.nb, 1, 0);
+    }
+    return n;
+  }
+  plan_tilings(&h, max_batch);
+  auto layer = [&](int l, const LayerRun& L) {
+    Launch r[2];
+    const int k = layer_launches(&h, L, batch, r);
+    for (int q = 0; q < k; ++q)
+      put(l, r[q].nb, r[q].small ? r[q].plan.rows : pd::kTileRows, r[q].small ? r[q].plan.cols : L.cw, r[q].parts,
+          !r[q].small && big_counts(&h, L, r[q].nb));
+  };
+  if (blocks) {
+    for (int k = 0; k < n_blocks; ++k) {
+      if (k > 0) layer(2 * k, block_conv(blocks[k], false));
+      if (k < n_blocks - 1) layer(2 * k + 1, block_conv(blocks[k], true));
+    }
+  } else {
+    const bool out5 = layers[n_layers - 1].k == 5;
+    for (int l = 1; l < n_layers - (out5 ? 0 : 1); ++l) layer(l, plain_layer(layers, n_layers, l));
+  }
+  return n;
+}
 
 const char* predecoder_status_string(pd_status s) {
   switch (s) {
@@ -1268,9 +1392,7 @@ pd_status predecoder_create_ex(const float* weights, size_t n_weights, int32_t d
   for (int i = 0; i < n_layers - 1; ++i) cmax = std::max(cmax, (int)layers[i].c_out);
   h->cmax = cmax;
   if (dtype != PD_DTYPE_FP32) {
-    h->tiling = plan_tiling(g, max_batch, ks);
-    h->sums = plan_tiling(g, max_batch, ks, true);
-    for (int k = 0; k < 3; ++k) h->small[k] = plan_small(g, 64 + 32 * k, ks);
+    plan_tilings(h, max_batch);
     const int max_span = ks == 3 ? std::min(pd::conv_single_max_span(), pd::conv_hidden_max_span(3))
                                  : pd::conv_hidden_max_span(5);
     if (h->tiling.span <= 0 || h->tiling.span > max_span) {
@@ -1508,9 +1630,7 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
     delete h;
     return PD_ERR_DEVICE;
   }
-  h->tiling = plan_tiling(g, max_batch);
-  h->sums = plan_tiling(g, max_batch, 3, true);
-  for (int k = 0; k < 3; ++k) h->small[k] = plan_small(g, 64 + 32 * k, 3);
+  plan_tilings(h, max_batch);
   if (h->tiling.span <= 0 || h->tiling.span > pd::conv_hidden_max_span(3)) {
     delete h;
     return PD_ERR_UNSUPPORTED;
@@ -1904,11 +2024,7 @@ bool same_sums(const pd_layer* layers, int n, int dtype, int layout, int d, int 
     h[k].sums = plan_tiling(h[k].g, Bs[k], h[k].ks, true);
   }
   for (int l = 1; l < n - 1; ++l) {
-    LayerRun L{};
-    L.cin = layers[l].c_in;
-    L.cout = layers[l].c_out;
-    L.cw = std::min(L.cout, 128);
-    L.carries_head = l == n - 2 && layers[n - 1].k == 1;
+    const LayerRun L = plain_layer(layers, n, l);
     const SumPlan a = sum_plan(&h[0], L, batch), b = sum_plan(&h[1], L, batch2);
     if (a.parts != b.parts || a.first != batch || b.first != batch2) return false;
   }

@@ -313,6 +313,30 @@ std::vector<float> conv_fp32_bias(const float* b, int cout, int head) {
   return r;
 }
 
+// Cycles of a 16-channel chunk: m n x 128 of MFMAs, or the four SIMDs' loads
+// through the CU's L1, where a block of voxels (16 rows in as many lines)
+// takes 64 and a weight block 16 -- 355 cycles were measured for 1 x 1
+// blocks.  Times the waves a SIMD runs one after the other; of equals the
+// larger tile.  A head needs all channel blocks in the wave (4 x 4 or 2 x 8
+// blocks fit the registers).
+Fp32Blocks conv_fp32_blocks(long long nvox, int cout, int head, int n_cu) {
+  const int nbt = (cout + 15) / 16;
+  const long long simds = 4ll * n_cu;
+  Fp32Blocks r{1, 1};
+  long long best = -1;
+  for (int m = 1; m <= 4; m *= 2)
+    for (int n = 1; n <= 8; ++n) {
+      if (m * n > 16 || (head ? n != nbt : n > std::min(nbt, 4))) continue;
+      const long long waves = (nvox + 16 * m - 1) / (16 * m) * ((nbt + n - 1) / n);
+      const long long cost = (waves + simds - 1) / simds * std::max(128 * m * n, 4 * (64 * m + 16 * n));
+      if (best < 0 || cost < best || (cost == best && m * n > r.mb * r.nb)) {
+        best = cost;
+        r = {m, n};
+      }
+    }
+  return r;
+}
+
 hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const float* x, float* y, const float* w,
                             const float* bias, int head, const float* head_w, const float* head_b,
                             const int32_t* tables, uint8_t* nib, float* logits, int batch, int n_cu,
@@ -322,26 +346,9 @@ hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const flo
   const long long nvox = (long long)batch * g.V;  // < 2^31 (host check)
   const int nbt = (cout + 15) / 16;
   const uint32_t wbytes = (uint32_t)(cin == 2 ? 7 * 512 : 27 * 64 * cin) * nbt;
-  // Blocks per wave.  Cycles of a 16-channel chunk: m n x 128 of MFMAs, or
-  // the four SIMDs' loads through the CU's L1, where a block of voxels (16
-  // rows in as many lines) takes 64 and a weight block 16 -- 355 cycles were
-  // measured for 1 x 1 blocks.  Times the waves a SIMD runs one after the
-  // other; of equals the larger tile.  A head needs all channel blocks in
-  // the wave (4 x 4 or 2 x 8 blocks fit the registers).
   const long long simds = 4ll * n_cu;
-  int mb = 1, nb = 1;
-  long long best = -1;
-  for (int m = 1; m <= 4; m *= 2)
-    for (int n = 1; n <= 8; ++n) {
-      if (m * n > 16 || (head ? n != nbt : n > std::min(nbt, 4))) continue;
-      const long long waves = (nvox + 16 * m - 1) / (16 * m) * ((nbt + n - 1) / n);
-      const long long cost = (waves + simds - 1) / simds * std::max(128 * m * n, 4 * (64 * m + 16 * n));
-      if (best < 0 || cost < best || (cost == best && m * n > mb * nb)) {
-        best = cost;
-        mb = m;
-        nb = n;
-      }
-    }
+  const Fp32Blocks bl = conv_fp32_blocks(nvox, cout, head, n_cu);
+  const int mb = bl.mb, nb = bl.nb;
   hipError_t err = hipErrorInvalidValue;
   auto launch = [&](auto M, auto N, auto F, auto E, auto HD) {
     constexpr int MB = decltype(M)::value, NB = decltype(N)::value;

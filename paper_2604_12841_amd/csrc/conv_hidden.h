@@ -51,6 +51,9 @@ struct HiddenCall {
 // halo of two; bf16 c_in = c_out = 64 or 128, epi 0).
 hipError_t launch_conv_hidden(const HiddenCall& c, bool fp8);
 
+// Whether a launch of nunits units on nwg workgroups takes units from counters.
+inline bool conv_hidden_counts(long long nunits, long long nwg) { return nunits > 2 * nwg; }
+
 // hipErrorInvalidValue for a call whose instance is not in the unit.
 template <bool F8>
 hipError_t launch_hidden_narrow(const HiddenCall& c);  // activations, 64 output channels

@@ -785,7 +785,7 @@ hipError_t launch_one(const HiddenCall& c) {
   const Tiling& tl = *c.tl;
   const long long nunits = tl.ntiles << c.lsl;
   const long long nwg = conv_workgroups(nunits, c.n_workgroups);
-  uint32_t* const sched = nunits <= 2 * nwg ? nullptr : c.sched;  // null: every unit is one of the two fixed ones
+  uint32_t* const sched = conv_hidden_counts(nunits, nwg) ? c.sched : nullptr;  // null: fixed shares
   // fixed units per workgroup before the counters: two on cells; on flat
   // tiles seven eighths of a workgroup's share
   const long long share = (nunits + 7) / 8 / (nwg / 8);

@@ -264,6 +264,12 @@ hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const flo
 std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout, int head);
 std::vector<float> conv_fp32_bias(const float* b, int cout, int head);
 
+// Blocks of a wave: mb x 16 voxels, nb x 16 channels.
+struct Fp32Blocks {
+  int mb, nb;
+};
+Fp32Blocks conv_fp32_blocks(long long nvox, int cout, int head, int n_cu);
+
 // The 1x1x1 head and the threshold over activation rows of c_in (64 or 128)
 // values, bf16 or E4M3.
 hipError_t launch_head(const Geom& g, int cin, const void* x, int fp8, const float* w_head, const float* b_head,

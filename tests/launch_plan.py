@@ -1,0 +1,26 @@
+"""The launches that the library plans for a network, asked of its host code (no GPU)."""
+import collections
+import ctypes
+
+import paper_2604_12841_amd as pdx
+
+# layer: of a plain network, or conv1 / conv2 of block k as 2 k / 2 k + 1; rows, cols: voxels and channels of a tile
+# (256 voxels: the persistent kernel; fp32: of a wave); parts: K parts of a sum; counters: units come from counters
+Launch = collections.namedtuple("Launch", "layer samples rows cols parts counters")
+
+
+def launches(d, T, dtype, batch, layers=None, blocks=None, layout="plaquette", max_batch=None, n_cu=256):
+    out = (ctypes.c_int32 * 1200)()
+    n = pdx.lib().pd_plan_launches(
+        pdx._layers(layers) if layers else None, len(layers or ()), pdx._blocks(blocks) if blocks else None,
+        len(blocks or ()), d, T, pdx._DTYPES[dtype], pdx._LAYOUTS[layout], batch, max_batch or batch, n_cu, out, 200)
+    assert 0 <= n <= 200, n
+    return [Launch(*out[6 * k:6 * k + 6]) for k in range(n)]
+
+
+def network(layout, widths, k=3, act=1):
+    layers, ci = [], 2 if layout == "plaquette" else 4
+    for w in widths:
+        layers.append((ci, w, k, act))
+        ci = w
+    return layers + [(ci, 4, 1 if layout == "plaquette" else k, 0)]

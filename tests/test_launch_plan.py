@@ -1,0 +1,37 @@
+"""CPU: the launches planned for the conv layers."""
+import pytest
+
+from launch_plan import launches, network
+from paper_2604_12841_amd import workload
+
+NETS = [("plaquette", network("plaquette", w), None, ("bf16", "fp8")) for w in ([64, 64, 64], [128, 128, 128],
+                                                                               [64, 128, 64], [128, 64, 128])]
+NETS += [("paper", network("paper", w), None, ("bf16", "fp8")) for w in ([128, 128], [256, 256, 256], [256, 256, 64])]
+NETS += [("paper", network("paper", [w, w], 5), None, ("bf16",)) for w in (64, 128)]
+NETS += [("paper", None, workload.resnet_blocks([w, w]), ("bf16", "fp8")) for w in (64, 128, 256, 512)]
+
+
+@pytest.mark.parametrize("net", NETS, ids=lambda n: "%s_%s" % (n[0], "x".join(str(l[1]) for l in n[1] or n[2])))
+def test_every_launch_has_a_tile(net):
+    """Samples add up, a tile's channels divide its slice, and some tile fits every grid and batch."""
+    layout, layers, blocks, dtypes = net
+    for dtype in dtypes:
+        for d in (3, 5, 9, 13, 21, 31, 63):
+            for T in (1, 2, 7, d, 1023):
+                for batch in (1, 2, 3, 7, 16, 50, 200):
+                    if batch > 1 and batch * T * d * d > 1 << 18:
+                        break
+                    plan = launches(d, T, dtype, batch, layers, blocks, layout)
+                    done = {}
+                    for r in plan:
+                        assert r.rows in (64, 96, 128, 256) and r.cols in (32, 64, 128) and r.parts >= 1, r
+                        assert dtype == "fp8" or r.rows < 256 or r.parts == 1, r
+                        done[r.layer] = done.get(r.layer, 0) + r.samples
+                    assert done and set(done.values()) == {batch}
+
+
+def test_fp32_blocks_cover_the_head():
+    for w in (8, 16, 40, 64, 72, 104, 128):
+        for batch in (1, 10, 100, 1000):
+            last = launches(5, 5, "fp32", batch, network("plaquette", [32, w]))[-1]
+            assert last.cols == (w + 15) // 16 * 16 and last.rows in (16, 32, 64)
