@@ -45,14 +45,21 @@ struct HiddenCall {
 // Weight fragments per slice in 16-channel chunks (conv_fragments in
 // api.hip; fp8: conv_fragments_fp8 in 32-channel chunks); n_workgroups =
 // conv_hidden_workgroups_per_cu() per CU; sched: 256 zeroed words (per XCD: a
-// grab and a done counter, 64 bytes apart): a launch of more than two units
+// grab and a done counter, 64 bytes apart): a launch of more than six units
 // per workgroup takes its units after the fixed ones from these counters and
 // leaves them zero; null: fixed shares.  ks: kernel size 3, or 5 (cells, a
 // halo of two; bf16 c_in = c_out = 64 or 128, epi 0).
 hipError_t launch_conv_hidden(const HiddenCall& c, bool fp8);
 
-// Whether a launch of nunits units on nwg workgroups takes units from counters.
-inline bool conv_hidden_counts(long long nunits, long long nwg) { return nunits > 2 * nwg; }
+// Whether a launch of nunits units on nwg workgroups takes units from
+// counters: from six units per workgroup on.  A unit is taken two ahead, so in
+// a short launch the units past the fixed ones all go to the workgroups that
+// started first, often both of one CU, while fixed shares spread them over the
+// CUs.  With counters from two / six units on: 1100 units of 256-wide layers
+// (Model 5 at d = 13, batch 64) 1891 / 1640 us, 1203 units in fp8 (Model 4 at d
+// = 13, batch 140) 694 / 631; from three on 2 % more than from six at five and
+// a half units (Model 4 at d = 13, batch 330), and no difference past six.
+inline bool conv_hidden_counts(long long nunits, long long nwg) { return nunits > 6 * nwg; }
 
 // hipErrorInvalidValue for a call whose instance is not in the unit.
 template <bool F8>

@@ -481,8 +481,8 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
 
   // Units: each XCD takes a contiguous range (tile_of).  A workgroup's first
   // nstat units are fixed (the k-th, (k + n)-th, ... of its XCD's range, n =
-  // the XCD's workgroups); with `sched` (a launch of more units than two per
-  // workgroup), the rest are taken in turn from a per-XCD counter, so that
+  // the XCD's workgroups); with `sched` (a launch that conv_hidden_counts says
+  // counts), the rest are taken in turn from a per-XCD counter, so that
   // workgroups that run faster take more of them (fixed shares left the
   // last workgroups of an XCD finishing 10-20 % of the layer after the
   // first).  Thread 0 takes unit it + 2 at the top of iteration it and hands

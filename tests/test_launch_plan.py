@@ -35,3 +35,13 @@ def test_fp32_blocks_cover_the_head():
         for batch in (1, 10, 100, 1000):
             last = launches(5, 5, "fp32", batch, network("plaquette", [32, w]))[-1]
             assert last.cols == (w + 15) // 16 * 16 and last.rows in (16, 32, 64)
+
+
+def test_short_launches_take_fixed_shares():
+    """Up to six units per workgroup (512 workgroups); 64 and 140 samples are 1100 and 1203 units."""
+    def counters(model, batch, dtype):
+        layers = workload.paper_model_layers(model)
+        return {r.counters for r in launches(13, 13, dtype, batch, layers, layout="paper") if r.rows == 256}
+
+    assert counters(5, 64, "bf16") == {0} and counters(4, 140, "fp8") == {0} and counters(4, 330, "bf16") == {0}
+    assert counters(5, 200, "bf16") == {1} and counters(4, 4096, "fp8") == {1}
