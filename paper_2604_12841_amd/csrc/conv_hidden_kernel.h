@@ -301,6 +301,16 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   // row wm ROWS + 32 mb + l32); ebuf: a staging buffer free for the
   // transposition / head partials.
   auto finish_tile = [&](int tile, int slice, lds_char* const ebuf, f32x16 (&acc)[MB][NB]) {
+      // The lane's place, made opaque for the wide and the shortcut-adding
+      // epilogues: their addresses would else be computed once before the K
+      // loop, spilled over it (up to 85 registers) and reloaded from memory in
+      // every tile (fp8 128 -> 128 at d = 13, batch 64: 84 us a layer, 72
+      // without).  A 64-wide layer has the registers, and loses 2-4 % when
+      // they are computed per tile.
+      int place = threadIdx.x;
+      if constexpr (COUT == 128 || EPI == EPI_ADD) asm volatile("" : "+v"(place));
+      const int tid = place, lane = tid & 63, wave = tid >> 6, wm = wave % W::WM, wn = wave / W::WM;
+      const int half = lane >> 5, l32 = lane & 31;
       // this slice's output columns, and its shortcut columns or projection rows
       char* const ysl = (char*)y + (size_t)slice * COUT * P::ESZ;
       const uint16_t* const scs = head_w ? sc : (const uint16_t*)((const char*)sc + (size_t)slice * COUT * P::ESZ);
