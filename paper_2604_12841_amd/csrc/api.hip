@@ -741,12 +741,15 @@ int conv_parts(const pd_predecoder* h, const LayerRun& L, long long tiles) {
 // ---- Which kernel runs a hidden layer: the persistent one (launch_conv_hidden:
 // 256-voxel tiles, two workgroups per CU; sums of one part) or the one for
 // small launches (launch_conv_small).  Both times are estimated in
-// microseconds and the smaller one wins.  The estimates follow MI355X
-// measurements per layer of 64-, 128- and 256-wide networks from d = 5 to 31
-// at batches 1 to 8 to about 15 %; at the line the two are as close
-// (small / persistent, 128 channels: bf16 45 / 48 us at 41k voxels, 76 / 78 at
-// 81k, 100 / 94 at 127k; fp8 42 / 50 at 81k, 62 / 56 at 127k; at 32k voxels
-// 27 / 48, fp8 19 / 32).  Past a full round of the persistent kernel's units it
+// microseconds and the smaller one wins.  Both were fitted to 1400 networks of
+// 64- to 512-wide layers timed on MI355X both ways, 20 to 512 units at d = 5 to
+// 31: what is taken is 1.6 % off the faster one on average.  Small / persistent
+// near the line, whole networks in us by the units of a layer: four 128-wide
+// layers bf16 122 / 152 at 120, 156 / 156 at 182, 203 / 171 at 228, 235 / 255 at
+// 288, 323 / 273 at 370; fp8 84 / 99 at 136, 112 / 106 at 184, 163 / 161 at
+// 371; 64-wide bf16 60 / 68 at 161, 119 / 112 at 410, fp8 57 / 55 at 256, 82 /
+// 73 at 360; two 512-wide blocks bf16 631 / 671 at 320, 892 / 766 at 480, fp8
+// 229 / 250 at 160, 495 / 414 at 360.  Past a full round of the persistent kernel's units it
 // always runs: small launches then cost 4 to 28 % more (networks of four layers
 // at 617 units: 128 channels bf16 510 / 426 us, fp8 311 / 260; 64 channels at 615
 // 166 / 159, at 3600 817 / 706), all but the first few units over.
@@ -817,9 +820,9 @@ BigTime big_time(const pd_predecoder* h, const LayerRun& L) {
   const int taps = h->ks * h->ks * h->ks;
   const double steps = fp8 ? L.cin / 32 * ((taps + 1) / 2) * 2.0 : L.cin / 16 * taps;
   const double m = steps * (L.cw / 16) * 32 / 2100.0;
-  if (h->ks == 5) return {1.4 * m, 1.4 * m, h->n_cu};
-  if (fp8) return {1.7 * m + 8.0, 3.6 * m + 7.0, 2ll * h->n_cu};
-  return {1.75 * m + (L.cw == 64 ? 8.0 : 3.0), 3.3 * m + 12.0, 2ll * h->n_cu};
+  if (h->ks == 5) return {1.15 * m, 1.15 * m, h->n_cu};
+  if (fp8) return {1.2 * m + 10.0, 2.9 * m + 6.0, 2ll * h->n_cu};
+  return {1.55 * m + (L.cw == 64 ? 11.0 : 4.0), 2.55 * m + 16.0, 2ll * h->n_cu};
 }
 
 double big_us(const BigTime& b, long long units) {  // units <= b.round

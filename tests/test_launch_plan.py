@@ -45,3 +45,25 @@ def test_short_launches_take_fixed_shares():
 
     assert counters(5, 64, "bf16") == {0} and counters(4, 140, "fp8") == {0} and counters(4, 330, "bf16") == {0}
     assert counters(5, 200, "bf16") == {1} and counters(4, 4096, "fp8") == {1}
+
+
+# Networks timed both ways (us: small-launch kernel / persistent kernel), well apart
+TIMED = [
+    ("w128", "bf16", 13, 37, 323, 273), ("w128", "bf16", 9, 94, 311, 265), ("w128", "bf16", 25, 6, 355, 287),
+    ("w128", "bf16", 13, 12, 122, 152), ("w128", "fp8", 13, 12, 83, 100),
+    ("w64", "bf16", 5, 718, 151, 129), ("w64", "bf16", 5, 171, 55, 65), ("w64", "fp8", 11, 60, 87, 71),
+    ("model2", "fp8", 11, 32, 234, 204), ("model2", "fp8", 7, 138, 255, 208), ("model2", "bf16", 13, 22, 425, 362),
+    ("model2", "fp8", 7, 45, 113, 127),
+    ("r512", "fp8", 13, 10, 495, 414), ("r512", "fp8", 7, 69, 480, 401), ("r512", "fp8", 17, 4, 543, 421),
+    ("r512", "bf16", 11, 20, 892, 766), ("r512", "bf16", 13, 6, 489, 436), ("r512", "fp8", 5, 61, 205, 252),
+    ("r128", "bf16", 13, 38, 490, 426), ("r128", "fp8", 7, 119, 161, 199),
+]
+
+
+@pytest.mark.parametrize("net,dtype,d,batch,small,persistent", TIMED, ids=lambda v: str(v))
+def test_the_faster_kernel_runs(net, dtype, d, batch, small, persistent):
+    layers = {"w128": network("plaquette", [128] * 4), "w64": network("plaquette", [64] * 4),
+              "model2": workload.paper_model_layers(2)}.get(net)
+    blocks = {"r512": workload.resnet_blocks([512] * 2), "r128": workload.resnet_blocks([128] * 3)}.get(net)
+    plan = launches(d, d, dtype, batch, layers, blocks, "plaquette" if net[0] == "w" else "paper")
+    assert {r.rows == 256 for r in plan if r.samples > batch // 2} == {persistent < small}, plan
