@@ -10,7 +10,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -2012,26 +2011,136 @@ struct pd_stream {
 };
 
 namespace {
-// Whether every hidden layer of a plain network sums `batch` samples of T
-// rounds in the parts that a batch of T2 rounds takes (no sample apart).
-bool same_sums(const pd_layer* layers, int n, int dtype, int layout, int d, int T, int batch, int T2, int batch2,
-               int n_cu) {
-  if (dtype != PD_DTYPE_BF16) return true;  // (fp32 sums do not depend on the batch; fp8 ones may)
-  pd_predecoder h[2];
-  const int Ts[2] = {T, T2}, Bs[2] = {batch, batch2};
-  for (int k = 0; k < 2; ++k) {
-    h[k].ks = network_ks(layers);
-    h[k].g = make_geom(d, Ts[k], layout, 0, 0, (h[k].ks - 1) / 2);
-    h[k].dtype = dtype;
-    h[k].n_cu = n_cu;
-    h[k].sums = plan_tiling(h[k].g, Bs[k], h[k].ks, true);
-  }
+// A plain network's run of `batch` samples as a handle would plan it (no device memory).
+struct PlannedRun {
+  pd_predecoder h;
+  int batch;
+};
+
+PlannedRun plan_run(const pd_layer* layers, int dtype, int layout, int d, int T, int batch, int n_cu) {
+  PlannedRun r;
+  r.h.ks = network_ks(layers);
+  r.h.g = make_geom(d, T, layout, 0, 0, (r.h.ks - 1) / 2);
+  r.h.dtype = dtype;
+  r.h.n_cu = n_cu;
+  r.batch = batch;
+  if (dtype != PD_DTYPE_FP32) plan_tilings(&r.h, batch);
+  return r;
+}
+
+// Whether every hidden layer of a plain bf16 network takes its sums in the
+// same parts in both runs (no sample apart).  (fp32 sums have one order; fp8
+// ones may differ in order between the kernels that two batch sizes run on, as
+// predecoder_run's do.)
+bool same_sums(const pd_layer* layers, int n, const PlannedRun& a, const PlannedRun& b) {
+  if (a.h.dtype != PD_DTYPE_BF16) return true;
   for (int l = 1; l < n - 1; ++l) {
     const LayerRun L = plain_layer(layers, n, l);
-    const SumPlan a = sum_plan(&h[0], L, batch), b = sum_plan(&h[1], L, batch2);
-    if (a.parts != b.parts || a.first != batch || b.first != batch2) return false;
+    const SumPlan p = sum_plan(&a.h, L, a.batch), q = sum_plan(&b.h, L, b.batch);
+    if (p.parts != q.parts || p.first != a.batch || q.first != b.batch) return false;
   }
   return true;
+}
+
+// Estimated microseconds of a run: its hidden layers as their launches are
+// chosen (small_us, big_us; past a round of units, full rounds and the rest),
+// and for the launches around them and the gaps between 50, and 0.4 ns per
+// voxel.  (Of 424 streams timed both ways, d = 5 to 31, it takes the slower way by
+// more than 5 % in 3.)
+double run_us(const pd_layer* layers, int n, const PlannedRun& r) {
+  const pd_predecoder& h = r.h;
+  double us = 50.0 + 4e-4 * r.batch * h.g.V;
+  for (int l = 1; l < n; ++l) {
+    if (l == n - 1 && layers[l].k != 5) break;  // (the head, or a 3x3x3 output layer: part of the above)
+    const LayerRun L = plain_layer(layers, n, l);
+    if (h.dtype == PD_DTYPE_FP32) {
+      const pd::Fp32Blocks b = pd::conv_fp32_blocks((long long)r.batch * h.g.V, L.cout, l == n - 2, h.n_cu);
+      us += 5.0 + b.cost * (27.0 * L.cin / 16.0) / 2100.0;
+      continue;
+    }
+    Launch q[2];
+    const int k = layer_launches(&h, L, r.batch, q);
+    for (int i = 0; i < k; ++i) {
+      if (q[i].small) {
+        us += small_us(&h, L, q[i].nb, q[i].parts, &q[i].plan);
+        continue;
+      }
+      Tiling t = h.tiling;
+      tiling_for_batch(&t, h.g, q[i].nb);
+      const BigTime bt = big_time(&h, L);
+      const long long units = t.ntiles * (L.cout / L.cw), rest = units % bt.round;
+      us += units / bt.round * bt.t2 + (rest ? big_us(bt, rest) : 0.0);
+    }
+  }
+  return us;
+}
+
+// The batches of a stream: its windows, per batch their length, count and
+// whether they touch the stream's first / last round, and the samples whose
+// geometric channels are cleared there (Geom::first_n, last_from).
+struct StreamPlan {
+  struct Batch {
+    int len, count, first, last;
+  };
+  std::vector<pd::StreamWindow> win;
+  std::vector<Batch> batches;
+  int first_n = INT_MAX, last_from = 0;
+};
+
+// n_cu 0: unknown, windows of one length and boundary kind per batch.
+StreamPlan plan_stream(const pd_layer* layers, int n_layers, int d, int n_rounds, int core, int buffer, int dtype,
+                       int layout, int n_streams, int n_cu) {
+  const int nw = predecoder_stream_windows(n_rounds, core, buffer, nullptr, nullptr, nullptr, nullptr, 0);
+  std::vector<int32_t> st(nw), ln(nw), cs(nw), cl(nw);
+  predecoder_stream_windows(n_rounds, core, buffer, st.data(), ln.data(), cs.data(), cl.data(), nw);
+  StreamPlan p;
+  // a batch per length, first-round window, last-round window (the paper
+  // layout clears its geometric channels only at the stream's own ends)
+  p.win.resize(nw);
+  for (int k = 0; k < nw; ++k) {
+    const int first = st[k] == 0, last = st[k] + ln[k] == n_rounds;
+    int b = 0;
+    while (b < (int)p.batches.size() &&
+           (p.batches[b].len != ln[k] || p.batches[b].first != first || p.batches[b].last != last))
+      ++b;
+    if (b == (int)p.batches.size()) p.batches.push_back({ln[k], 0, first, last});
+    p.win[k] = pd::StreamWindow{st[k], ln[k], cs[k], cl[k], b, p.batches[b].count++};
+  }
+  // All windows as one batch of the longest window's length: the shorter ones,
+  // at the stream's ends, read further rounds that their cores do not depend
+  // on (the buffer reaches the receptive field), and the geometric channels
+  // are cleared for the first / last windows' samples.  One run then takes
+  // the place of up to five, four of them a few windows each (Model 4, d =
+  // 13, bf16, two streams of 1000 rounds: 3.36 -> 2.99 ms).  Only where no
+  // bf16 sum's parts change, and where the further rounds cost less than the
+  // launches saved: a few windows of many streams fill the chip anyway (64
+  // streams of 39 rounds, three windows: 3.17 ms in three batches, 3.76 in one
+  // of 29 % more rounds).
+  int reach = 0;
+  for (int l = 0; l < n_layers; ++l) reach += (layers[l].k - 1) / 2;
+  if (n_cu < 1 || p.batches.size() < 2 || buffer < reach || !layer_chain_ok(layers, n_layers, layout)) return p;
+  const int len = *std::max_element(ln.begin(), ln.end());
+  const Geom whole = make_geom(d, len, layout, 0, 0, (network_ks(layers) - 1) / 2);
+  if (!supported(whole, layers, n_layers, dtype) || (long long)nw * n_streams * whole.S >= (1ll << 30)) return p;
+  const PlannedRun all = plan_run(layers, dtype, layout, d, len, nw * n_streams, n_cu);
+  double batches_us = 0.0;
+  for (const auto& b : p.batches) {
+    const PlannedRun run = plan_run(layers, dtype, layout, d, b.len, b.count * n_streams, n_cu);
+    if (!same_sums(layers, n_layers, run, all)) return p;
+    batches_us += run_us(layers, n_layers, run);
+  }
+  if (run_us(layers, n_layers, all) >= batches_us) return p;
+  p.batches.assign(1, {len, nw, 1, 1});
+  int firsts = 0, lasts = 0;
+  for (int k = 0; k < nw; ++k) {
+    const int start = std::min(st[k], n_rounds - len);
+    firsts += start == 0;
+    lasts += start + len == n_rounds;
+    p.win[k] = pd::StreamWindow{start, len, cs[k], cl[k], 0, k};
+  }
+  p.first_n = firsts * n_streams;
+  p.last_from = (nw - lasts) * n_streams;
+  return p;
 }
 
 void stream_free(pd_stream* s) {
@@ -2052,6 +2161,15 @@ void stream_free(pd_stream* s) {
 
 extern "C" {
 
+// For the tests: the batches that a stream's windows run in, planned without
+// a device for one of n_cu compute units; -1 for arguments without a plan.
+int32_t pd_plan_stream(const pd_layer* layers, int32_t n_layers, int32_t d, int32_t n_rounds, int32_t core,
+                       int32_t buffer, int32_t dtype, int32_t layout, int32_t n_streams, int32_t n_cu) {
+  if (predecoder_stream_windows(n_rounds, core, buffer, nullptr, nullptr, nullptr, nullptr, 0) < 1) return -1;
+  return (int32_t)plan_stream(layers, n_layers, d, n_rounds, core, buffer, dtype, layout, n_streams, n_cu)
+      .batches.size();
+}
+
 pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32_t d, int32_t n_rounds, int32_t core,
                                    int32_t buffer, const pd_layer* layers, int32_t n_layers, int32_t dtype,
                                    int32_t n_streams, const pd_options* opts, pd_stream** out) {
@@ -2062,8 +2180,12 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
   const pd_options o = opts ? *opts : pd_options{PD_LAYOUT_PLAQUETTE, PD_BOUNDARY_NONE, PD_BOUNDARY_NONE};
   const int32_t nw = predecoder_stream_windows(n_rounds, core, buffer, nullptr, nullptr, nullptr, nullptr, 0);
   if (nw < 1) return PD_ERR_INVALID_ARG;
-  std::vector<int32_t> st(nw), ln(nw), cs(nw), cl(nw);
-  predecoder_stream_windows(n_rounds, core, buffer, st.data(), ln.data(), cs.data(), cl.data(), nw);
+  int n_cu = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    n_cu = 0;
+  (void)hipGetLastError();
+  const StreamPlan plan = plan_stream(layers, n_layers, d, n_rounds, core, buffer, dtype, o.layout, n_streams, n_cu);
   pd_stream* s = new (std::nothrow) pd_stream();
   if (!s) return PD_ERR_OUT_OF_MEMORY;
   s->d = d;
@@ -2071,56 +2193,11 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
   s->core = core;
   s->buffer = buffer;
   s->n_streams = n_streams;
-  // group key: length, first-round window, last-round window (the paper
-  // layout clears its geometric channels only at the stream's own ends)
-  std::vector<std::array<int, 3>> keys;
-  s->win.resize(nw);
-  for (int k = 0; k < nw; ++k) {
-    const std::array<int, 3> key{ln[k], st[k] == 0, st[k] + ln[k] == n_rounds};
-    int gi = (int)(std::find(keys.begin(), keys.end(), key) - keys.begin());
-    if (gi == (int)keys.size()) {
-      keys.push_back(key);
-      s->groups.emplace_back();
-      s->groups.back().len = ln[k];
-    }
-    s->win[k] = pd::StreamWindow{st[k], ln[k], cs[k], cl[k], gi, s->groups[gi].count++};
-  }
-  // All windows as one batch of the longest window's length: the shorter ones,
-  // at the stream's ends, read further rounds that their cores do not depend
-  // on (the buffer reaches the receptive field), and the geometric channels
-  // are cleared for the first / last windows' samples.  One run then takes
-  // the place of up to five, four of them a few windows each (Model 4, d =
-  // 13, two streams of 1000 rounds, bf16: 3.38 -> 2.89 ms).  Only where no sum's parts
-  // change.
-  int reach = 0;
-  for (int l = 0; l < n_layers; ++l) reach += (layers[l].k - 1) / 2;
-  int n_cu = 0, dev = 0;
-  bool merge = keys.size() > 1 && buffer >= reach && layer_chain_ok(layers, n_layers, o.layout) &&
-               hipGetDevice(&dev) == hipSuccess &&
-               hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n_cu > 0;
-  const int len = *std::max_element(ln.begin(), ln.end());
-  if (merge) {
-    const Geom whole = make_geom(d, len, o.layout, 0, 0, (network_ks(layers) - 1) / 2);
-    merge = supported(whole, layers, n_layers, dtype) && (long long)nw * n_streams * whole.S < (1ll << 30);
-    for (const auto& G : s->groups)
-      merge = merge && same_sums(layers, n_layers, dtype, o.layout, d, G.len, G.count * n_streams, len, nw * n_streams,
-                                 n_cu);
-  }
-  int first_n = INT_MAX, last_from = 0;
-  if (merge) {
-    keys.assign(1, {len, 1, 1});
-    s->groups.assign(1, pd_stream::Group());
-    s->groups[0].len = len;
-    s->groups[0].count = nw;
-    int firsts = 0, lasts = 0;
-    for (int k = 0; k < nw; ++k) {
-      const int start = std::min(st[k], n_rounds - len);
-      firsts += start == 0;
-      lasts += start + len == n_rounds;
-      s->win[k] = pd::StreamWindow{start, len, cs[k], cl[k], 0, k};
-    }
-    first_n = firsts * n_streams;
-    last_from = (nw - lasts) * n_streams;
+  s->win = plan.win;
+  for (const auto& b : plan.batches) {
+    s->groups.emplace_back();
+    s->groups.back().len = b.len;
+    s->groups.back().count = b.count;
   }
   pd_status r = PD_OK;
   auto fail = [&](pd_status e) {
@@ -2130,12 +2207,12 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
   for (size_t gi = 0; gi < s->groups.size(); ++gi) {
     auto& G = s->groups[gi];
     pd_options go = o;
-    if (!keys[gi][1]) go.first_round = PD_BOUNDARY_NONE;
-    if (!keys[gi][2]) go.last_round = PD_BOUNDARY_NONE;
+    if (!plan.batches[gi].first) go.first_round = PD_BOUNDARY_NONE;
+    if (!plan.batches[gi].last) go.last_round = PD_BOUNDARY_NONE;
     r = predecoder_create_ex(weights, n_weights, d, G.len, layers, n_layers, dtype, G.count * n_streams, &go, &G.h);
     if (r != PD_OK) return fail(r);
-    G.h->g.first_n = first_n;
-    G.h->g.last_from = last_from;
+    G.h->g.first_n = plan.first_n;
+    G.h->g.last_from = plan.last_from;
     const size_t rows = (size_t)G.count * n_streams;
     if ((r = dev_alloc(&G.det, rows * predecoder_det_words(d, G.len) * 8)) != PD_OK) return fail(r);
     if ((r = dev_alloc(&G.flips, rows * predecoder_flip_words(d, G.len) * 8)) != PD_OK) return fail(r);

@@ -322,17 +322,13 @@ std::vector<float> conv_fp32_bias(const float* b, int cout, int head) {
 Fp32Blocks conv_fp32_blocks(long long nvox, int cout, int head, int n_cu) {
   const int nbt = (cout + 15) / 16;
   const long long simds = 4ll * n_cu;
-  Fp32Blocks r{1, 1};
-  long long best = -1;
+  Fp32Blocks r{1, 1, -1};
   for (int m = 1; m <= 4; m *= 2)
     for (int n = 1; n <= 8; ++n) {
       if (m * n > 16 || (head ? n != nbt : n > std::min(nbt, 4))) continue;
       const long long waves = (nvox + 16 * m - 1) / (16 * m) * ((nbt + n - 1) / n);
       const long long cost = (waves + simds - 1) / simds * std::max(128 * m * n, 4 * (64 * m + 16 * n));
-      if (best < 0 || cost < best || (cost == best && m * n > r.mb * r.nb)) {
-        best = cost;
-        r = {m, n};
-      }
+      if (r.cost < 0 || cost < r.cost || (cost == r.cost && m * n > r.mb * r.nb)) r = {m, n, cost};
     }
   return r;
 }

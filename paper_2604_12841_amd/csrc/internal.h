@@ -264,9 +264,11 @@ hipError_t launch_conv_fp32(const Geom& g, int cin, int cout, int act, const flo
 std::vector<float> conv_fp32_fragments(const float* w, int cin, int cout, int head);
 std::vector<float> conv_fp32_bias(const float* b, int cout, int head);
 
-// Blocks of a wave: mb x 16 voxels, nb x 16 channels.
+// Blocks of a wave: mb x 16 voxels, nb x 16 channels; cycles of a 16-channel
+// chunk on a SIMD.
 struct Fp32Blocks {
   int mb, nb;
+  long long cost;
 };
 Fp32Blocks conv_fp32_blocks(long long nvox, int cout, int head, int n_cu);
 

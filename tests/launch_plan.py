@@ -24,3 +24,9 @@ def network(layout, widths, k=3, act=1):
         layers.append((ci, w, k, act))
         ci = w
     return layers + [(ci, 4, 1 if layout == "plaquette" else k, 0)]
+
+
+def stream_batches(layers, d, n_rounds, core, buffer, dtype, n_streams, layout="paper", n_cu=256):
+    """Batches that a stream's windows run in."""
+    return pdx.lib().pd_plan_stream(pdx._layers(layers), len(layers), d, n_rounds, core, buffer, pdx._DTYPES[dtype],
+                                    pdx._LAYOUTS[layout], n_streams, n_cu)

@@ -12,6 +12,7 @@ import pytest
 import oracle
 import paper_2604_12841_amd as pdx
 from paper_2604_12841_amd import workload
+from launch_plan import stream_batches
 from parity import assert_parity, compare, dev_u64, host_u64, run_gpu, say
 
 torch = pytest.importorskip("torch")
@@ -37,6 +38,8 @@ def test_windows_in_one_batch(cuda, d, n, core, buffer, B, first, last, dtype):
     weights = workload.he_normal_weights(layers, 401)
     det, _ = workload.make_inputs(d, n, B, 0.02, 0.02, 402)
     say("stream", d, n, core, buffer, B, first, last, dtype)
+    assert stream_batches(layers, d, n, core, buffer, dtype, B) == 1
+    assert stream_batches(layers, d, n, core, buffer, dtype, B, n_cu=0) > 1
     s = pdx.Stream(weights, d, n, layers, core, buffer, dtype, n_streams=B, layout="paper", first=first, last=last)
     flips = torch.full((B, s.flip_words), -1, dtype=torch.int64, device="cuda")
     res = torch.full((B, s.det_words), -1, dtype=torch.int64, device="cuda")

@@ -1,7 +1,7 @@
 """CPU: the launches planned for the conv layers."""
 import pytest
 
-from launch_plan import launches, network
+from launch_plan import launches, network, stream_batches
 from paper_2604_12841_amd import workload
 
 NETS = [("plaquette", network("plaquette", w), None, ("bf16", "fp8")) for w in ([64, 64, 64], [128, 128, 128],
@@ -67,3 +67,28 @@ def test_the_faster_kernel_runs(net, dtype, d, batch, small, persistent):
     blocks = {"r512": workload.resnet_blocks([512] * 2), "r128": workload.resnet_blocks([128] * 3)}.get(net)
     plan = launches(d, d, dtype, batch, layers, blocks, "plaquette" if net[0] == "w" else "paper")
     assert {r.rows == 256 for r in plan if r.samples > batch // 2} == {persistent < small}, plan
+
+
+# Streams timed both ways, core = buffer = d (us: one batch / a batch per length and boundary kind)
+STREAMS = [
+    (1, "fp8", 13, 39, 4, 146, 190), (1, "bf16", 13, 39, 8, 327, 402), (4, "bf16", 13, 65, 8, 920, 1165),
+    (4, "fp8", 13, 100, 8, 764, 1045), (1, "fp8", 5, 200, 1, 55, 180), (1, "bf16", 21, 150, 1, 428, 548),
+    (4, "bf16", 13, 39, 64, 3765, 3174), (4, "bf16", 21, 50, 16, 3227, 2849), (4, "fp8", 21, 50, 16, 1809, 1664),
+    (1, "bf16", 31, 93, 2, 931, 857), (4, "bf16", 31, 93, 16, 12817, 10228), (4, "fp8", 31, 93, 16, 7140, 5632),
+]
+
+
+@pytest.mark.parametrize("model,dtype,d,rounds,streams,merged,batches", STREAMS, ids=lambda v: str(v))
+def test_stream_windows_merge_where_it_is_faster(model, dtype, d, rounds, streams, merged, batches):
+    got = stream_batches(workload.paper_model_layers(model), d, rounds, d, d, dtype, streams)
+    assert (got == 1) == (merged < batches), got
+
+
+def test_stream_windows_that_do_not_merge():
+    """A buffer below the receptive field (5 of Model 4), no device, windows that are all alike."""
+    layers = workload.paper_model_layers(4)
+    assert stream_batches(layers, 13, 1000, 13, 13, "bf16", 2) == 1
+    assert stream_batches(layers, 13, 1000, 13, 5, "bf16", 2) > 1
+    assert stream_batches(layers, 13, 1000, 13, 13, "bf16", 2, n_cu=0) == 5
+    assert stream_batches(layers, 13, 13, 13, 13, "bf16", 2) == 1
+    assert stream_batches(layers, 13, 0, 13, 13, "bf16", 2) == -1
