@@ -2170,21 +2170,10 @@ int32_t pd_plan_stream(const pd_layer* layers, int32_t n_layers, int32_t d, int3
       .batches.size();
 }
 
-pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32_t d, int32_t n_rounds, int32_t core,
-                                   int32_t buffer, const pd_layer* layers, int32_t n_layers, int32_t dtype,
-                                   int32_t n_streams, const pd_options* opts, pd_stream** out) {
-  if (!out) return PD_ERR_INVALID_ARG;
-  *out = nullptr;
-  if (!weights || !layers || n_rounds < 1 || core < 1 || buffer < 0 || n_streams < 1) return PD_ERR_INVALID_ARG;
-  if (d < 3 || d % 2 == 0 || n_rounds > kMaxT) return d < 3 || d % 2 == 0 ? PD_ERR_INVALID_ARG : PD_ERR_UNSUPPORTED;
-  const pd_options o = opts ? *opts : pd_options{PD_LAYOUT_PLAQUETTE, PD_BOUNDARY_NONE, PD_BOUNDARY_NONE};
-  const int32_t nw = predecoder_stream_windows(n_rounds, core, buffer, nullptr, nullptr, nullptr, nullptr, 0);
-  if (nw < 1) return PD_ERR_INVALID_ARG;
-  int n_cu = 0, dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    n_cu = 0;
-  (void)hipGetLastError();
+// predecoder_stream_create with its arguments checked and its windows planned for n_cu compute units.
+static pd_status create_stream(const float* weights, size_t n_weights, int32_t d, int32_t n_rounds, int32_t core,
+                               int32_t buffer, const pd_layer* layers, int32_t n_layers, int32_t dtype,
+                               int32_t n_streams, const pd_options& o, int n_cu, pd_stream** out) {
   const StreamPlan plan = plan_stream(layers, n_layers, d, n_rounds, core, buffer, dtype, o.layout, n_streams, n_cu);
   pd_stream* s = new (std::nothrow) pd_stream();
   if (!s) return PD_ERR_OUT_OF_MEMORY;
@@ -2237,6 +2226,29 @@ pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32
   if (hipDeviceSynchronize() != hipSuccess) return fail(PD_ERR_DEVICE);
   *out = s;
   return PD_OK;
+}
+
+pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32_t d, int32_t n_rounds, int32_t core,
+                                   int32_t buffer, const pd_layer* layers, int32_t n_layers, int32_t dtype,
+                                   int32_t n_streams, const pd_options* opts, pd_stream** out) {
+  if (!out) return PD_ERR_INVALID_ARG;
+  *out = nullptr;
+  if (!weights || !layers || n_rounds < 1 || core < 1 || buffer < 0 || n_streams < 1) return PD_ERR_INVALID_ARG;
+  if (d < 3 || d % 2 == 0 || n_rounds > kMaxT) return d < 3 || d % 2 == 0 ? PD_ERR_INVALID_ARG : PD_ERR_UNSUPPORTED;
+  const pd_options o = opts ? *opts : pd_options{PD_LAYOUT_PLAQUETTE, PD_BOUNDARY_NONE, PD_BOUNDARY_NONE};
+  const int32_t nw = predecoder_stream_windows(n_rounds, core, buffer, nullptr, nullptr, nullptr, nullptr, 0);
+  if (nw < 1) return PD_ERR_INVALID_ARG;
+  int n_cu = 0, dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    n_cu = 0;
+  (void)hipGetLastError();
+  pd_status r = create_stream(weights, n_weights, d, n_rounds, core, buffer, layers, n_layers, dtype, n_streams, o,
+                              n_cu, out);
+  // (one batch needs a little more memory than several)
+  if (r == PD_ERR_OUT_OF_MEMORY && n_cu > 0)
+    r = create_stream(weights, n_weights, d, n_rounds, core, buffer, layers, n_layers, dtype, n_streams, o, 0, out);
+  return r;
 }
 
 pd_status predecoder_stream_run(pd_stream* s, void* hip_stream, const uint64_t* det, uint64_t* flips,
