@@ -1244,6 +1244,9 @@ int n_stop_points(const pd_predecoder* h) {
 
 extern "C" {
 
+// For the tests: workgroups of 256 threads of the head's kernel.
+int64_t pd_head_blocks(int64_t voxels, int32_t c_in, int32_t fp8) { return pd::head_blocks(voxels, c_in, fp8); }
+
 // For the tests: the launches that a network's layers (blocks given: a
 // residual network's convs) after the first take at `batch` samples on a
 // handle for max_batch, planned without a device for one of n_cu compute

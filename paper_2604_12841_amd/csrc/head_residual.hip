@@ -30,7 +30,8 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 // A voxel's row of activations (bf16, or F8 E4M3 codes) is read 16 bytes per
 // lane by consecutive lanes, whose partial sums of the four logits are then
 // added; the first of them thresholds and stores.  cin: 64 or 128, so a row
-// is 4, 8 or 16 lanes.
+// is 4, 8 or 16 lanes.  Workgroups stride over the rows (a grid's threads
+// are counted in 32 bits, a batch's rows x 16 lanes are not).
 template <bool F8>
 __global__ void __launch_bounds__(256) head_kernel(Geom g, int cin, const void* __restrict__ x,
                                                    const float* __restrict__ w_head, const float* __restrict__ b_head,
@@ -38,45 +39,47 @@ __global__ void __launch_bounds__(256) head_kernel(Geom g, int cin, const void* 
                                                    float* __restrict__ logits, int batch) {
   constexpr int CPL = F8 ? 16 : 8;  // channels per lane
   const int lpr = cin / CPL;        // lanes per row (a power of two)
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long u = gid / lpr;
-  const bool real = u < (long long)batch * g.V;
-  const int c0 = (int)(gid - u * lpr) * CPL;
-  const int b = (int)((real ? u : 0) / g.V);
-  const int v = (int)((real ? u : 0) - (long long)b * g.V);
+  const int c0 = (int)(threadIdx.x % lpr) * CPL;
+  const long long rows = (long long)batch * g.V, step = (long long)gridDim.x * (blockDim.x / lpr);
   const int HH = g.H * g.H;
-  const int t = v / HH, s = v - t * HH;
-  const int i = s / g.H, j = s - i * g.H;
-  const u32x4 q = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(x) +
-                                                  (padded_index(g, b, t, i, j) * cin + c0) * (F8 ? 1 : 2));
-  float a[CPL];
+  // (a row's lanes take the same turns: 256 is a multiple of lpr)
+  for (long long u = (long long)blockIdx.x * (blockDim.x / lpr) + threadIdx.x / lpr; u < rows; u += step) {
+    const int b = (int)(u / g.V);
+    const int v = (int)(u - (long long)b * g.V);
+    const int t = v / HH, s = v - t * HH;
+    const int i = s / g.H, j = s - i * g.H;
+    const u32x4 q = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(x) +
+                                                    (padded_index(g, b, t, i, j) * cin + c0) * (F8 ? 1 : 2));
+    float a[CPL];
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    if constexpr (F8) {
-      a[4 * h] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 0);
-      a[4 * h + 1] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 1);
-      a[4 * h + 2] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 2);
-      a[4 * h + 3] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 3);
-    } else {
-      a[2 * h] = __uint_as_float(q[h] << 16);
-      a[2 * h + 1] = __uint_as_float(q[h] & 0xffff0000u);
+    for (int h = 0; h < 4; ++h) {
+      if constexpr (F8) {
+        a[4 * h] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 0);
+        a[4 * h + 1] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 1);
+        a[4 * h + 2] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 2);
+        a[4 * h + 3] = __builtin_amdgcn_cvt_f32_fp8((int)q[h], 3);
+      } else {
+        a[2 * h] = __uint_as_float(q[h] << 16);
+        a[2 * h + 1] = __uint_as_float(q[h] & 0xffff0000u);
+      }
     }
-  }
-  float lg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float lg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int e = 0; e < CPL; ++e)
+    for (int e = 0; e < CPL; ++e)
 #pragma unroll
-    for (int o = 0; o < 4; ++o) lg[o] = fmaf(w_head[o * cin + c0 + e], a[e], lg[o]);
-  for (int m = lpr >> 1; m >= 1; m >>= 1)
+      for (int o = 0; o < 4; ++o) lg[o] = fmaf(w_head[o * cin + c0 + e], a[e], lg[o]);
+    for (int m = lpr >> 1; m >= 1; m >>= 1)
 #pragma unroll
-    for (int o = 0; o < 4; ++o) lg[o] += __shfl_xor(lg[o], m);
-  if (!real || c0 != 0) return;
+      for (int o = 0; o < 4; ++o) lg[o] += __shfl_xor(lg[o], m);
+    if (c0 == 0) {
 #pragma unroll
-  for (int o = 0; o < 4; ++o) lg[o] += b_head[o];
-  nib[u] = (uint8_t)flip_nibble(g, tables, i, j, lg);
-  if (logits) {
+      for (int o = 0; o < 4; ++o) lg[o] += b_head[o];
+      nib[u] = (uint8_t)flip_nibble(g, tables, i, j, lg);
+      if (logits) {
 #pragma unroll
-    for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + s] = lg[o];
+        for (int o = 0; o < 4; ++o) logits[(((long long)b * 4 + o) * g.T + t) * HH + s] = lg[o];
+      }
+    }
   }
 }
 
@@ -270,11 +273,15 @@ __global__ void __launch_bounds__(256) residual_from_flips_kernel(Geom g, const 
   if (lane == 0) residual[(long long)b * g.Wd + w] = m;
 }
 
+long long head_blocks(long long voxels, int cin, int fp8) {
+  constexpr long long kMost = 1 << 16;  // 256 workgroups per CU
+  return std::min((voxels * (cin / (fp8 ? 16 : 8)) + 255) / 256, kMost);
+}
+
 hipError_t launch_head(const Geom& g, int cin, const void* x, int fp8, const float* w_head, const float* b_head,
                        const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream) {
   if (cin != 64 && cin != 128) return hipErrorInvalidValue;
-  const long long threads = (long long)batch * g.V * (cin / (fp8 ? 16 : 8));
-  const dim3 grid((unsigned)((threads + 255) / 256));
+  const dim3 grid((unsigned)head_blocks((long long)batch * g.V, cin, fp8));
   if (fp8)
     hipLaunchKernelGGL(head_kernel<true>, grid, dim3(256), 0, stream, g, cin, x, w_head, b_head, tables, nib, logits,
                        batch);

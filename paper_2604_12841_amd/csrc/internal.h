@@ -277,6 +277,8 @@ Fp32Blocks conv_fp32_blocks(long long nvox, int cout, int head, int n_cu);
 hipError_t launch_head(const Geom& g, int cin, const void* x, int fp8, const float* w_head, const float* b_head,
                        const int32_t* tables, uint8_t* nib, float* logits, int batch, hipStream_t stream);
 
+long long head_blocks(long long voxels, int cin, int fp8);  // its workgroups of 256 threads
+
 hipError_t launch_residual_pack(const Geom& g, const int32_t* tables, const uint64_t* det,
                                 const uint8_t* nib, uint64_t* flips, uint64_t* residual, int batch,
                                 hipStream_t stream);

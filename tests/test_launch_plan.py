@@ -1,6 +1,9 @@
 """CPU: the launches planned for the conv layers."""
+import ctypes
+
 import pytest
 
+import paper_2604_12841_amd as pdx
 from launch_plan import launches, network, stream_batches
 from paper_2604_12841_amd import workload
 
@@ -92,3 +95,14 @@ def test_stream_windows_that_do_not_merge():
     assert stream_batches(layers, 13, 1000, 13, 13, "bf16", 2, n_cu=0) == 5
     assert stream_batches(layers, 13, 13, 13, 13, "bf16", 2) == 1
     assert stream_batches(layers, 13, 0, 13, 13, "bf16", 2) == -1
+
+
+def test_head_threads_fit_32_bits():
+    f = pdx.lib().pd_head_blocks
+    f.restype, f.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32]
+    for c_in in (64, 128):
+        for fp8 in (0, 1):
+            for voxels in (1, 1000, 1 << 20, 1 << 28, (1 << 31) - 1):
+                assert 1 <= f(voxels, c_in, fp8) <= (2 ** 32 - 1) // 256
+            lanes = c_in // (16 if fp8 else 8)
+            assert f(1000, c_in, fp8) == -(-1000 * lanes // 256)
