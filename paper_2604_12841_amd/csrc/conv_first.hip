@@ -34,6 +34,7 @@
 
 #include "activation.h"
 #include "internal.h"
+#include "lds_limit.h"
 
 namespace pd {
 namespace {
@@ -354,9 +355,8 @@ hipError_t launch_conv_first(const Geom& g, int cin, int cout, int slices, size_
     static_assert(pl0 % 8 == 0 && pl0 + kFirstRange * I * 2 <= 160 * 1024, "LDS");
     const auto kernel = conv_first_kernel<I, C, decltype(A)::value, decltype(E)::value, KZ, decltype(FU)::value>;
     if (pl0 + kFirstRange * I * 2 > 64 * 1024) {  // more than 64 KB of LDS
-      static const hipError_t attr = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                         pl0 + kFirstRange * I * 2);
-      if ((err = attr) != hipSuccess) return;
+      static std::atomic<uint64_t> done{0};
+      if ((err = allow_lds((const void*)kernel, pl0 + kFirstRange * I * 2, done)) != hipSuccess) return;
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)nblk, (unsigned)slices), dim3(64 * W), lds, stream, g, planes, y, ystride,
                        (const u32x4*)wfrag, bias, dc, (int)nvox, bpw, hsplit, wslice, pk, range, pl0);

@@ -52,6 +52,7 @@
 
 #include "activation.h"
 #include "conv_hidden.h"
+#include "lds_limit.h"
 #include "shortcut.h"
 #include "tiles.h"
 
@@ -784,14 +785,13 @@ conv_hidden_kernel(Geom g, Tiling tl, int act, const void* __restrict__ x, void*
   finish_sched();
 }
 
-// Launches one instance of the hidden kernel (the LDS size attribute set on
-// its first use).
+// Launches one instance of the hidden kernel.
 template <int CIN, int COUT, int EPI, int MODE, bool F8, int KS>
 hipError_t launch_one(const HiddenCall& c) {
   using L = Lds<COUT, KS>;
-  static const hipError_t attr = hipFuncSetAttribute((const void*)conv_hidden_kernel<CIN, COUT, EPI, MODE, F8, KS>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, L::total);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<uint64_t> done{0};
+  const hipError_t e = allow_lds((const void*)conv_hidden_kernel<CIN, COUT, EPI, MODE, F8, KS>, L::total, done);
+  if (e != hipSuccess) return e;
   const Tiling& tl = *c.tl;
   const long long nunits = tl.ntiles << c.lsl;
   const long long nwg = conv_workgroups(nunits, c.n_workgroups);

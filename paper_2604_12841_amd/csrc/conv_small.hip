@@ -42,6 +42,7 @@
 
 #include "activation.h"
 #include "conv_small.h"
+#include "lds_limit.h"
 #include "shortcut.h"
 #include "tiles.h"
 
@@ -448,9 +449,9 @@ conv_small_kernel(SmallArgs p) {
 
 template <typename S, int EPI>
 hipError_t launch(const SmallArgs& a, long long blocks, hipStream_t stream) {
-  static const hipError_t attr = hipFuncSetAttribute((const void*)conv_small_kernel<S, EPI>,
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, S::lds);
-  if (attr != hipSuccess) return attr;
+  static std::atomic<uint64_t> done{0};
+  const hipError_t e = allow_lds((const void*)conv_small_kernel<S, EPI>, S::lds, done);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((conv_small_kernel<S, EPI>), dim3((unsigned)blocks), dim3(NT), S::lds, stream, a);
   return hipGetLastError();
 }
