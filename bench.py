@@ -417,7 +417,8 @@ def main():
         # input planes; residual+repack reads the flip nibbles (one byte per
         # voxel) and the detectors and writes the packed flip and residual rows
         "stage_gbs": {
-            "unpack": B * (pre.det_words * 8 + V * in_bytes) / (stages[0] * 1e-3) / 1e9,
+            # (null where layer 1 reads the packed events itself)
+            "unpack": B * (pre.det_words * 8 + V * in_bytes) / (stages[0] * 1e-3) / 1e9 if stages[0] > 0 else None,
             "residual_repack": B * (V + pre.det_words * 16 + pre.flip_words * 8) / (stages[n + 1] * 1e-3) / 1e9,
         },
         "graph_replays": None if replays is None else dict(

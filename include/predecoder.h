@@ -238,8 +238,9 @@ int32_t predecoder_num_stages(const pd_predecoder* h);
 
 /* Runs the full path n_iter times on hip_stream with HIP events between the
  * stages and writes the mean milliseconds of each stage to ms_per_stage
- * (host, predecoder_num_stages(h) floats).  Arguments as predecoder_run
- * (logits not written).  Blocks the host until the stream has drained. */
+ * (host, predecoder_num_stages(h) floats).  On small launches layer 1 reads
+ * the packed events itself; no kernel unpacks them, and stage 0 is 0.
+ * Arguments as predecoder_run (logits not written).  Blocks the host until the stream has drained. */
 pd_status predecoder_stage_times(pd_predecoder* h, void* hip_stream, const uint64_t* det,
                                  int32_t batch, uint64_t* flips, uint64_t* residual, int32_t n_iter,
                                  float* ms_per_stage);

@@ -1127,6 +1127,15 @@ pd_status enqueue_resnet(pd_predecoder* h, Workspace& ws, hipStream_t st, const 
   return mark();
 }
 
+// Whether layer 1 unpacks the events itself (small launches; not the fp32 one,
+// nor a plaquette network's only hidden layer, which carries the head unless
+// the run stops at it).
+bool layer1_unpacks(const pd_predecoder* h, int batch, int stop) {
+  if (!h->blocks.empty() || h->dtype == PD_DTYPE_FP32) return false;
+  const bool single = h->layers.size() == 2 && h->layers[1].k == 1 && h->layers[0].c_in == 2 && stop < 0;
+  return !single && pd::conv_first_fuses(h->g, batch, h->ks);
+}
+
 // Enqueues the whole path in workspace ws.  ev (optional) receives one event
 // record before each stage and one after the last.  stop >= 0: stop after
 // that hidden layer (residual networks: that conv, see enqueue_resnet), whose
@@ -1152,9 +1161,7 @@ pd_status enqueue_run(pd_predecoder* h, Workspace& ws, hipStream_t st, const uin
   };
   pd_status s;
   if ((s = mark()) != PD_OK) return s;
-  // (small launches: layer 1 unpacks the events itself)
-  const bool single = n == 2 && !out3 && h->layers[0].c_in == 2 && stop < 0;  // layer 1 carries the head
-  const bool fused = !fp32 && !single && pd::conv_first_fuses(g, batch, ks);
+  const bool fused = layer1_unpacks(h, batch, stop);
   if (!fused) s = check_launch(pd::launch_unpack(g, h->tables, det, batch, ws.planes, 1, fp32, st));
   if (s != PD_OK) return s;
   const void* x = ws.planes;
@@ -1909,6 +1916,7 @@ pd_status predecoder_stage_times(pd_predecoder* h, void* hip_stream, const uint6
         }
         ms_per_stage[k] += ms / n_iter;
       }
+    if (layer1_unpacks(h, batch, -1)) ms_per_stage[0] = 0.0f;  // no kernel between the first two events
   }
   for (auto& e : ev)
     if (e) (void)hipEventDestroy(e);

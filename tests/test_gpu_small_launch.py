@@ -137,3 +137,17 @@ def test_resnet_96_voxel_tiles(cuda):
     """Two-part layers with a shortcut (its row, or its projection) in the epilogue."""
     resnets.test_resnet_convs_tight(cuda, dict(name="w128_two_parts", blocks=workload.resnet_blocks([128, 128]), d=9,
                                                T=9, B=24, layout="paper"))
+
+
+@pytest.mark.parametrize("dtype,B,unpacks", [("bf16", 1, False), ("fp8", 2, False), ("bf16", 128, True), ("fp32", 1, True)])
+def test_unpack_stage(cuda, dtype, B, unpacks):
+    """Stage 0 takes no time exactly where layer 1 reads the packed events itself."""
+    d = 9
+    layers = network("plaquette", [64, 64])
+    pre = pdx.Predecoder(workload.he_normal_weights(layers, 1), d, d, layers, dtype, max_batch=B)
+    det = dev_u64(workload.make_inputs(d, d, B, 0.02, 0.02, 2)[0])
+    flips = torch.empty((B, pre.flip_words), dtype=torch.int64, device="cuda")
+    res = torch.empty((B, pre.det_words), dtype=torch.int64, device="cuda")
+    ms = pre.stage_times(det, flips, res, 3)
+    assert (ms[0] > 0) == unpacks and all(t > 0 for t in ms[1:3]), ms
+    pre.close()
