@@ -33,6 +33,7 @@ PEAK_HBM_GBS = 8000.0
 # source and every header it includes.
 KERNEL_SOURCES = ("paper_2604_12841_amd/csrc/conv_hidden_wide_bf16.hip",
                   "paper_2604_12841_amd/csrc/conv_hidden_kernel.h", "paper_2604_12841_amd/csrc/conv_hidden.h",
+                  "paper_2604_12841_amd/csrc/lds_limit.h", "paper_2604_12841_amd/csrc/shortcut.h",
                   "paper_2604_12841_amd/csrc/tiles.h", "paper_2604_12841_amd/csrc/activation.h",
                   "paper_2604_12841_amd/csrc/internal.h", "include/predecoder.h")
 
