@@ -30,3 +30,22 @@ def stream_batches(layers, d, n_rounds, core, buffer, dtype, n_streams, layout="
     """Batches that a stream's windows run in."""
     return pdx.lib().pd_plan_stream(pdx._layers(layers), len(layers), d, n_rounds, core, buffer, pdx._DTYPES[dtype],
                                     pdx._LAYOUTS[layout], n_streams, n_cu)
+
+
+def small_instances(d, T, dtype, batch, layers=None, blocks=None, layout="plaquette"):
+    """Instances of the small-launch kernel that a network's launches run: (dtype, kernel size, pieces of an input row
+    (half, one, more), voxels, channels, parts of a sum (fp8: 0, over 4: 8, over 16: 32), epilogue)."""
+    out = set()
+    for r in launches(d, T, dtype, batch, layers, blocks, layout):
+        if r.rows == 256:
+            continue
+        if blocks:
+            ci, ks, epi = blocks[r.layer // 2][r.layer % 2], 3, "add" if r.layer % 2 else "act"
+        else:
+            ci, co, ks = layers[r.layer][:3]
+            head = layers[-1][2] == 1 and r.layer == len(layers) - 2
+            epi = "out" if r.layer == len(layers) - 1 else "head" if head and co == 64 else "act"
+        row = ci * (1 if dtype == "fp8" else 2)
+        parts = 0 if dtype == "fp8" else r.parts if r.parts <= 4 else 8 if r.parts <= 16 else 32
+        out.add((dtype, ks, "half" if row < 128 else "one" if row == 128 else "more", r.rows, r.cols, parts, epi))
+    return out

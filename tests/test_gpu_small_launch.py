@@ -3,15 +3,17 @@
 Every hidden layer's stored activations are recomputed in fp64 from the GPU's
 own input (the planes, then what the GPU stored for the layer before) under
 the rule of tests/tight.py, whose bounds hold for any order of a sum's parts.
-The networks and batches reach the kernel's K parts (1 to 16, by how few tiles
-a launch has), its tile shapes, input rows of half a piece to four pieces, 3x3x3
-and 5x5x5 layers, one-round and ragged grids; the last cases run the
-persistent kernel on cells whose tiles start and end inside a round."""
+The networks and batches reach every instance of the kernel that the choice of
+launches takes (tests/test_launch_plan.py checks that they do): its K parts, tile
+shapes and epilogues, input rows of half a piece to four pieces, 3x3x3 and 5x5x5
+layers, on one-round and ragged grids; CASES holds at last some of the persistent kernel
+on cells whose tiles start and end inside a round."""
 import numpy as np
 import pytest
 
 import paper_2604_12841_amd as pdx
 import test_gpu_model6 as resnets
+import test_gpu_model6_fp8 as resnets_fp8
 import tight
 from paper_2604_12841_amd import workload
 from parity import dev_u64, say
@@ -54,7 +56,7 @@ CASES = [
     ("plaquette", [64, 64, 64], 3, 5, 5, 1, "bf16"),        # four parts of one chunk
     ("plaquette", [128, 128, 128], 3, 5, 1, 1, "bf16"),     # eight parts, one round of syndrome
     ("plaquette", [128, 128, 128], 3, 13, 13, 1, "bf16"),   # four parts
-    ("plaquette", [128, 64, 128], 3, 17, 17, 1, "bf16"),    # two parts, mixed widths
+    ("plaquette", [128, 64, 128], 3, 17, 17, 1, "bf16"),    # four parts, then one; mixed widths
     ("plaquette", [64, 64, 64], 3, 21, 9, 2, "bf16"),       # one part, 64-channel head in the tile
     ("plaquette", [128, 128, 128], 3, 25, 14, 1, "bf16"),   # one part, 128-channel head after the layer
     ("plaquette", [64, 64], 3, 63, 3, 1, "bf16"),           # the widest grid
@@ -69,6 +71,33 @@ CASES = [
     ("paper", [64, 64, 64], 5, 5, 4, 1, "bf16"),            # 5x5x5, one piece
     ("paper", [128, 128, 128], 5, 9, 9, 1, "bf16"),         # ... eight parts
     ("paper", [128, 128], 5, 13, 6, 3, "bf16"),
+    # the other instances, the smallest launches that reach them: 64-channel heads in the tile, by parts and tiles
+    ("plaquette", [128, 128, 64], 3, 3, 1, 36, "bf16"),
+    ("plaquette", [128, 128, 64], 3, 3, 2, 72, "bf16"),
+    ("plaquette", [128, 128, 64], 3, 3, 2, 250, "bf16"),
+    ("plaquette", [128, 128, 64], 3, 3, 5, 150, "bf16"),
+    ("plaquette", [128, 128, 64], 3, 3, 1, 72, "bf16"),
+    ("plaquette", [128, 128, 64], 3, 5, 2, 150, "bf16"),
+    ("plaquette", [64, 64, 64], 3, 3, 5, 150, "bf16"),
+    ("paper", [64, 256], 3, 3, 1, 250, "bf16"),
+    # fp8 128 x 64 tiles (a wide grid of one round)
+    ("plaquette", [64, 64, 64], 3, 43, 1, 16, "fp8"),
+    ("plaquette", [128, 128, 64], 3, 43, 1, 16, "fp8"),
+    # 5x5x5 layers of one piece, and of two
+    ("paper", [64, 64], 5, 3, 1, 72, "bf16"),
+    ("paper", [64, 64], 5, 3, 1, 150, "bf16"),
+    ("paper", [64, 64], 5, 5, 3, 72, "bf16"),
+    ("paper", [64, 64], 5, 5, 3, 150, "bf16"),
+    ("paper", [64, 64], 5, 11, 1, 48, "bf16"),
+    ("paper", [64, 64], 5, 11, 1, 100, "bf16"),
+    ("paper", [64, 64], 5, 21, 2, 16, "bf16"),
+    ("paper", [128, 128], 5, 3, 1, 36, "bf16"),
+    ("paper", [128, 128], 5, 3, 1, 72, "bf16"),
+    ("paper", [128, 128], 5, 3, 1, 150, "bf16"),
+    ("paper", [128, 128], 5, 5, 3, 36, "bf16"),
+    ("paper", [128, 128], 5, 5, 3, 150, "bf16"),
+    ("paper", [128, 128], 5, 11, 1, 24, "bf16"),
+    ("paper", [128, 128], 5, 11, 1, 36, "bf16"),
     # 96-voxel tiles of two parts
     ("paper", [128, 128, 128], 5, 13, 13, 8, "bf16"),
     ("paper", [128, 128], 5, 9, 7, 24, "bf16"),
@@ -131,6 +160,33 @@ def test_layers_tight(cuda, layout, widths, k, d, T, B, dtype):
     assert bool((err <= eps).all())
     assert bool(torch.isfinite(logits).all())
     pre.close()
+
+
+def _resnet(widths, d, T, B, dtype):
+    blocks, ci = [], 4
+    for w in widths:
+        blocks.append((ci, w, w, G))
+        ci = w
+    blocks.append((ci, ci, 4, G))
+    return dict(name="w%s_d%d_T%d_B%d_%s" % ("_".join(map(str, widths)), d, T, B, dtype), blocks=blocks, d=d, T=T, B=B,
+                layout="paper", dtype=dtype)
+
+
+# Layers with a shortcut, and a widening block's first (two parts of one piece)
+SHORTCUT_CASES = [_resnet(*c) for c in [
+    ([64, 128], 3, 1, 72, "bf16"), ([64, 128], 3, 5, 400, "bf16"), ([64, 128], 9, 1, 72, "bf16"),
+    ([64, 128], 43, 1, 4, "bf16"),
+    ([128, 64], 5, 3, 250, "bf16"), ([128, 64], 3, 1, 36, "bf16"), ([128, 64], 3, 1, 150, "bf16"),
+    ([128, 64], 3, 3, 72, "bf16"), ([128, 64], 9, 1, 36, "bf16"), ([128, 64], 9, 1, 150, "bf16"),
+    ([64], 3, 3, 150, "bf16"), ([256], 9, 1, 150, "bf16"),
+    ([64], 3, 1, 400, "fp8"), ([64], 43, 1, 16, "fp8"), ([128], 3, 1, 1, "fp8"), ([128], 3, 1, 150, "fp8"),
+    ([128], 43, 1, 8, "fp8"), ([256], 5, 3, 36, "fp8"),
+]]
+
+
+@pytest.mark.parametrize("case", SHORTCUT_CASES, ids=[c["name"] for c in SHORTCUT_CASES])
+def test_shortcut_layers_tight(cuda, case):
+    (resnets.test_resnet_convs_tight if case["dtype"] == "bf16" else resnets_fp8.test_resnet_fp8_convs_tight)(cuda, case)
 
 
 def test_resnet_96_voxel_tiles(cuda):

@@ -4,7 +4,7 @@ import ctypes
 import pytest
 
 import paper_2604_12841_amd as pdx
-from launch_plan import launches, network, stream_batches
+from launch_plan import launches, network, small_instances, stream_batches
 from paper_2604_12841_amd import workload
 
 NETS = [("plaquette", network("plaquette", w), None, ("bf16", "fp8")) for w in ([64, 64, 64], [128, 128, 128],
@@ -106,3 +106,51 @@ def test_head_threads_fit_32_bits():
                 assert 1 <= f(voxels, c_in, fp8) <= (2 ** 32 - 1) // 256
             lanes = c_in // (16 if fp8 else 8)
             assert f(1000, c_in, fp8) == -(-1000 * lanes // 256)
+
+
+# Networks and sizes whose launches reach the small-launch kernel's instances
+REACH_NETS = [(a, network(a, w, k), None, ("bf16",) if k == 5 else ("bf16", "fp8")) for a, w, k in [
+    ("plaquette", [64, 64, 64], 3), ("plaquette", [128, 128, 64], 3), ("plaquette", [64, 128, 128], 3),
+    ("paper", [256, 256, 64], 3), ("paper", [64, 256], 3), ("paper", [64, 64], 5), ("paper", [128, 128], 5)]]
+REACH_NETS += [("paper", None, workload.resnet_blocks([w, w]), ("bf16", "fp8")) for w in (64, 128, 256, 512)]
+REACH_NETS += [("paper", None, [(4, a, a, 1), (a, b, b, 1), (b, b, 4, 1)], ("bf16",)) for a, b in ((64, 128), (128, 64))]
+REACH_SIZES = [(d, T, b) for d in (3, 5, 9, 11, 13, 21, 31, 43) for T in sorted({1, 2, 3, 5, d})
+               for b in (1, 2, 3, 4, 6, 8, 11, 16, 24, 36, 48, 72, 100, 150, 250, 400)
+               if b == 1 or b * T * d * d < 150000]
+
+
+def test_every_small_launch_instance_is_tested():
+    """What the networks and sizes above reach is run by the GPU tests' cases."""
+    pytest.importorskip("torch")
+    import test_gpu_small_launch as cases
+    from resnet_cases import RESNET_CASES, RESNET_FP8_CASES
+    tested = set()
+    for layout, widths, k, d, T, batch, dtype in cases.CASES:
+        tested |= small_instances(d, T, dtype, batch, network(layout, widths, k), None, layout)
+    for c in RESNET_CASES + cases.SHORTCUT_CASES + [dict(c, dtype="fp8") for c in RESNET_FP8_CASES]:
+        tested |= small_instances(c["d"], c["T"], c.get("dtype", "bf16"), c["B"], None, c["blocks"], c["layout"])
+    reached = set()
+    for layout, layers, blocks, dtypes in REACH_NETS:
+        for dtype in dtypes:
+            for d, T, batch in REACH_SIZES:
+                reached |= small_instances(d, T, dtype, batch, layers, blocks, layout)
+    assert len(reached) > 80 and reached <= tested, sorted(reached - tested)
+
+
+def test_the_fp32_tests_run_every_kind_of_tile():
+    """Tiles of 16 to 64 voxels by 16 to 128 channels: layer 1, chunks of 8 and 16 channels, the head."""
+    pytest.importorskip("torch")
+    import test_gpu_fp32 as cases
+
+    def tiles(widths, d, T, batch):
+        layers = network("plaquette", widths)
+        for r in launches(d, T, "fp32", batch, layers):
+            ci = layers[r.layer][0]
+            yield ("first" if ci == 2 else "c8" if ci % 16 else "c16", r.layer == len(widths) - 1, r.rows, r.cols)
+
+    tested = {t for c in cases.CASES + cases.TILES for t in tiles(*c)}
+    reached = {t for w in ([8] * 2, [24] * 3, [32] * 4, [64] * 6, [40, 56, 64], [72, 104, 120], [96, 112, 128], [128] * 2,
+                           [16, 48, 80], [64], [128], [24], [48], [80])
+               for d in (3, 5, 9, 13) for batch in (1, 4, 16, 32, 64, 128, 200, 300) for t in tiles(w, d, d, batch)
+               if batch * d * (d + 1) ** 2 < 200000}
+    assert reached <= tested, sorted(reached - tested)
