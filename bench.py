@@ -238,8 +238,8 @@ def bench_stream(args, torch, pdx, workload):
         "dtype": {"bf16": "bf16", "fp8": "fp8-e4m3"}[dtype],
         "data": "synthetic (seeded phenomenological noise p=q=0.003, He-normal random weights)",
         "config": {"workload": "%d stream(s) of %d rounds at d=%d, Model %d (%s); %d windows per stream (core %d, "
-                               "buffer %d rounds; exact for buffer >= %d), all run on one GPU as one batch per "
-                               "window length" % (B, n, d, args.paper_model, layers, nwin, core, buf, h),
+                               "buffer %d rounds; exact for buffer >= %d), all run on one GPU, in one batch or one "
+                               "per window length and boundary kind" % (B, n, d, args.paper_model, layers, nwin, core, buf, h),
                    "d": d, "rounds": n, "streams": B, "model": args.paper_model, "windows_per_stream": nwin,
                    "core": core, "buffer": buf, "computed_rounds_per_stream": sum(w[1] for w in plan)},
         "us_per_round_per_stream": ms * 1e3 / n / B,

@@ -75,8 +75,10 @@
  * Precision.  PD_DTYPE_BF16: weights and every conv/head input are rounded
  * to bf16 (round to nearest even), products are accumulated in fp32, biases
  * and the activation are fp32, logits are fp32.  PD_DTYPE_FP32: fp32 end to
- * end.  flip = (logit > 0); a logit of exactly 0 is no flip.  Results are
- * bit-reproducible for a given handle and batch size; small batches split the
+ * end, every sum one chain of fused multiply-adds from its bias over the taps
+ * and, in each, the input channels in order, at every batch size.
+ * flip = (logit > 0); a logit of exactly 0 is no flip.  Results are
+ * bit-reproducible for a given handle and batch size; small bf16 batches split the
  * conv K loops over the waves of a workgroup, so two batch sizes can differ in
  * the fp32 summation order, and through an activation rounded to the other bf16
  * neighbour, by up to a few 1e-3 in the logits.
@@ -366,11 +368,16 @@ pd_status predecoder_create_resnet(const float* weights, size_t n_weights, int32
  * (k - 1) / 2 rounds from a window edge equals the output of one run over the
  * whole stream, so with buffer >= h the stitched cores are the whole-stream
  * corrections (up to the rounding-order rule of the handle's precision).  The
- * paper uses core = buffer = d (d x d x 3d blocks).  Windows are run as one
- * batch per window length (all windows of all streams at once: the paper
- * decodes the commit and cleanup blocks concurrently on several GPUs, or
- * several per GPU with a larger batch); the residual is then computed once
- * over the stitched flips of the whole stream. */
+ * paper uses core = buffer = d (d x d x 3d blocks).  Windows of one length and
+ * boundary kind, of all streams, run as one batch (the paper decodes the commit
+ * and cleanup blocks concurrently on several GPUs, or several per GPU with a
+ * larger batch).  Where the buffer reaches h, all windows may run as a single
+ * batch: those at the stream's ends, which are shorter, then read further
+ * rounds of the stream up to the common length, on which their cores do not
+ * depend.  The library does so where it estimates that to be faster and, in
+ * bf16, where no sum is split differently for it (fp8 sums may be taken in
+ * another order, as between two batch sizes).  The residual is then computed
+ * once over the stitched flips of the whole stream. */
 typedef struct pd_stream pd_stream; /* opaque */
 
 /* The window plan (host only): fills starts / lengths / core_starts /
@@ -385,7 +392,7 @@ int32_t predecoder_stream_windows(int32_t n_rounds, int32_t core, int32_t buffer
  * rounds at distance d: the arguments of predecoder_create_ex (weights
  * copied; the same precisions, layouts and shapes), plus the window plan.
  * opts->first_round / last_round apply to the windows at the stream's ends.
- * Creates one handle per window length; allocates device memory. */
+ * Creates a handle per batch of windows; allocates device memory. */
 pd_status predecoder_stream_create(const float* weights, size_t n_weights, int32_t d, int32_t n_rounds,
                                    int32_t core, int32_t buffer, const pd_layer* layers, int32_t n_layers,
                                    int32_t dtype, int32_t n_streams, const pd_options* opts, pd_stream** out);

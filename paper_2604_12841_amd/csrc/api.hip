@@ -706,7 +706,10 @@ struct LayerRun {
 // the counts that fit, the least estimate in microseconds of a unit's time:
 // its 16-channel chunks (2.5 each for 32 or 64 output channels, 3.9 for 128;
 // a 5x5x5 chunk has 125 taps instead of 27) and its epilogue, or a part's
-// share of the chunks and what parting costs.
+// share of the chunks and what parting costs.  (These are times of 256-voxel
+// units in slices of 32 to 128 channels whose parts met through memory, which
+// is how parted sums ran before the small-launch kernel; the choice stays as
+// it was so that results keep their bits.)
 int split_parts(const pd_predecoder* h, long long tiles, int cin, int width, int nsl, double* unit_us = nullptr) {
   const bool fp8 = h->dtype == PD_DTYPE_FP8;  // 32-channel chunks
   const int nch = cin / (fp8 ? 32 : 16);
@@ -891,8 +894,11 @@ pd_status run_big(const pd_predecoder* h, Workspace& ws, const LayerRun& L, floa
 // one to four times over and leave a short remainder, which would take a
 // whole unit's time with most of the chip idle, the last few samples take
 // parts and run on the small-launch kernel -- for long units only (512 input
-// channels in bf16): the second launch and the parts cost about 45 us.
-// (Model 6 at 13^3, batch 16: 552 units on 512 slots, the last 2 samples.)
+// channels): the second launch and the parts cost about 45 us.  (Model 6 at
+// 13^3, batch 16: 552 units on 512 slots, the last 2 samples.  Three blocks of
+// 512 channels with the remainder apart / in the one launch: bf16 d = 7, batch
+// 96 1610 / 1936 us, d = 9, batch 52 1867 / 2005, fp8 d = 7, batch 104 948 / 1056;
+// even at worst over 25 sizes.)
 constexpr long long kMaxTailRounds = 4;  // past this, a remainder costs little
 constexpr double kTailCostUs = 45.0;
 
@@ -2001,9 +2007,9 @@ int32_t predecoder_stream_windows(int32_t n_rounds, int32_t core, int32_t buffer
 
 }  // extern "C"
 
-// Temporal window driver: windows of the planner grouped by (length,
-// touches round 0, touches the last round); one handle per group runs all
-// its windows of all streams as one batch.
+// Temporal window driver: a handle per group of windows (those of one length
+// that touch round 0 / the last round alike, or all of them, see
+// plan_stream) runs them for all streams as one batch.
 struct pd_stream {
   int d = 0, n_rounds = 0, core = 0, buffer = 0, n_streams = 0;
   pd::Geom g;                          // the whole stream (for its residual)

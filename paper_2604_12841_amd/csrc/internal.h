@@ -214,8 +214,8 @@ hipError_t launch_proj(const Geom& g, const void* x, int cin, int xstride, const
 // Temporal windows over a stream of rounds (Sec. VI, parallel windows in
 // time): window k covers rounds [start, start + len) of every stream and
 // commits its core rounds [core_start, core_start + core_len); it is row
-// `slot * n_streams + s` of its group's batch (group: the windows of one
-// length and boundary kind, run by one handle).
+// `slot * n_streams + s` of its group's batch (group: the windows that one
+// handle runs).
 struct StreamWindow {
   int start, len, core_start, core_len, group, slot;
 };
