@@ -769,7 +769,7 @@ constexpr SmallShape kSmallBf16[] = {
     {1, 64, 64, 16, 4.5, 3.7, 1.1}, {1, 128, 64, 32, 4.3, 7.3}, {1, 128, 128, 64, 6.0, 9.5},
     {2, 64, 32, 16, 3.9, 2.7},  {2, 64, 64, 32, 4.0, 5.0},  {2, 128, 64, 64, 4.5, 5.0},
     {2, 96, 128, 96, 6.0, 7.2},
-    {4, 64, 32, 32, 3.9, 1.65}, {4, 64, 64, 64, 3.6, 2.7},  {4, 128, 32, 64, 4.0, 3.0}};
+    {4, 64, 32, 32, 3.9, 1.65}, {4, 64, 64, 64, 3.05, 2.7}, {4, 96, 64, 96, 5.5, 3.26}, {4, 128, 32, 64, 3.6, 2.63}};
 constexpr SmallShape kSmallFp8[] = {{4, 64, 32, 32, 4.5, 1.35}, {4, 64, 64, 64, 4.4, 2.35}, {4, 128, 64, 128, 5.4, 4.4}};
 constexpr SmallShape kSmall5[] = {
     {1, 64, 64, 16, 5.0, 14.5}, {1, 128, 64, 32, 5.0, 26.3}, {1, 128, 128, 64, 6.0, 43.0},
@@ -785,10 +785,15 @@ double small_us(const pd_predecoder* h, const LayerRun& L, int batch, int parts,
   auto consider = [&](const SmallShape& s) {
     const Tiling& t = h->small[s.rows / 32 - 2];
     if (s.kg != kg || t.span == 0 || L.cw % s.cols != 0 || (parts > 4 && !fp8 && s.rows != 64)) return;
-    if (s.rows == 96 && row <= 128) return;  // (two 128 x 64 tiles share a CU there, which is no slower)
+    // (two 128 x 64 tiles share a CU there, which is no slower; with four parts,
+    // two 64 x 64 ones of one-piece rows, and rows of two pieces were not measured)
+    if (s.rows == 96 && row <= (kg == 4 ? 256 : 128)) return;
     // (a fused head needs all channels in the tile; wider ones take a kernel of their own)
     if (L.carries_head && cout == 64 && s.cols != 64) return;
     const long long units = (long long)batch * t.ntT * t.ntI * t.ntJ * (cout / s.cols);
+    // (256 channels, us, 64 x 32 / 96 x 64 tiles: Model 5 d = 9, batch 6, 192 tiles 149 / 128, d = 17, 240 163 / 124, d
+    // = 7, batch 16, 256 165 / 169; 512 channels gain at 256 tiles too, 171 / 145)
+    if (s.rows == 96 && kg == 4 && row <= 512 && 16 * units > 15ll * h->n_cu) return;
     const int per_cu = pd::conv_small_occupancy(h->ks, row <= 128, s.acc);
     const long long rounds = (units + (long long)h->n_cu * per_cu - 1) / ((long long)h->n_cu * per_cu);
     const long long turns = (units + h->n_cu - 1) / h->n_cu;  // workgroups a CU runs

@@ -38,6 +38,12 @@
 // than the CUs: Model 3 at d = 13, batch 8 (its 128-wide 5x5x5 layers, 184
 // tiles instead of 288) 250 -> 207 us, Model 6 at 13^3, batch 16 (the last two
 // samples of the 512-wide layers) 2740 -> 2545.
+// Four parts of 256 channels and more take 96 x 64 tiles where those leave CUs free
+// (512 channels: fit them once; 64 x 32 ones are three times as many, two to a CU):
+// a wave's nine steps of weights in flight last 0.8 us of MFMAs there, about a first
+// read from memory, 64 x 32 tiles' 0.3.  In us, 64 x 32 / 96 x 64 (and 256-voxel tiles with their
+// K loops split over workgroups, before this kernel): Model 6 at 13^3, batch 1 417
+// / 288 (406), Model 5 at 17^3 163 / 124 (208), Model 2 at 13^3, batch 2 98 / 74 (107).
 #include <algorithm>
 
 #include "activation.h"
@@ -466,7 +472,7 @@ bool try_shape(const SmallArgs& a, long long blocks, const SmallPlan& pl, int ep
     *e = launch<S, 0>(a, blocks, stream);
     return true;
   }
-  if constexpr (KS == 3 && S::TC == 64) {
+  if constexpr (KS == 3 && S::TC == 64 && S::R != 96) {  // (heads follow 64 or 128 input channels)
     if (epi == 1 && a.ncg == 1) {
       *e = launch<S, 1>(a, blocks, stream);
       return true;
@@ -505,6 +511,9 @@ hipError_t launch_bf16(const SmallArgs& a, long long n, const SmallPlan& pl, int
       (void)(try_shape<KS, false, false, ONE, 2, false, 1, 2, 3, 2>(a, n, pl, epi, st, &e) ||
              try_shape<KS, false, false, ONE, 4, true, 1, 1, 2, 1>(a, n, pl, epi, st, &e) ||
              try_shape<KS, false, false, ONE, 4, true, 1, 1, 2, 2>(a, n, pl, epi, st, &e));
+  }
+  if constexpr (!ONE && KS == 3) {
+    if (e == hipErrorInvalidValue) (void)try_shape<KS, false, false, ONE, 4, false, 1, 1, 3, 2>(a, n, pl, epi, st, &e);
   }
   return e;
 }

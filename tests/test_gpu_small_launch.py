@@ -102,6 +102,9 @@ CASES = [
     ("paper", [128, 128, 128], 5, 13, 13, 8, "bf16"),
     ("paper", [128, 128], 5, 9, 7, 24, "bf16"),
     ("paper", [128, 256, 128], 3, 17, 17, 4, "bf16"),
+    # ... and of four parts: one round of the syndrome, a ragged last tile
+    ("paper", [256, 256], 3, 17, 1, 11, "bf16"),
+    ("paper", [256, 256], 3, 13, 13, 2, "bf16"),
     # the persistent kernel on cells
     ("plaquette", [64, 64], 3, 19, 19, 70, "bf16"),
     ("plaquette", [128, 128], 3, 21, 5, 200, "bf16"),
@@ -179,6 +182,7 @@ SHORTCUT_CASES = [_resnet(*c) for c in [
     ([128, 64], 5, 3, 250, "bf16"), ([128, 64], 3, 1, 36, "bf16"), ([128, 64], 3, 1, 150, "bf16"),
     ([128, 64], 3, 3, 72, "bf16"), ([128, 64], 9, 1, 36, "bf16"), ([128, 64], 9, 1, 150, "bf16"),
     ([64], 3, 3, 150, "bf16"), ([256], 9, 1, 150, "bf16"),
+    ([256], 13, 2, 11, "bf16"), ([512], 9, 2, 11, "bf16"),
     ([64], 3, 1, 400, "fp8"), ([64], 43, 1, 16, "fp8"), ([128], 3, 1, 1, "fp8"), ([128], 3, 1, 150, "fp8"),
     ([128], 43, 1, 8, "fp8"), ([256], 5, 3, 36, "fp8"),
 ]]

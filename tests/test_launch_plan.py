@@ -72,6 +72,21 @@ def test_the_faster_kernel_runs(net, dtype, d, batch, small, persistent):
     assert {r.rows == 256 for r in plan if r.samples > batch // 2} == {persistent < small}, plan
 
 
+# Layers of four parts timed in their tiles (us: 64 x 32, 64 x 64, 128 x 32, 96 x 64)
+TILES = [("model6", 13, 1, 417, 445, 407, 288), ("model5", 5, 64, 228, 190, 271, 225), ("model5", 13, 2, 168, 171, 171, 122),
+         ("model2", 17, 1, 96, 99, 99, 77), ("model2", 15, 2, 105, 98, 102, 112), ("r512", 5, 24, 165, 177, 181, 196),
+         ("r512", 7, 8, 171, 182, 177, 145), ("model5", 11, 4, 161, 168, 187, 145), ("model5", 7, 16, 165, 170, 176, 169)]
+
+
+@pytest.mark.parametrize("net,d,batch,t64x32,t64x64,t128x32,t96x64", TILES, ids=lambda v: str(v))
+def test_the_fastest_tile_runs(net, d, batch, t64x32, t64x64, t128x32, t96x64):
+    layers = {"model2": workload.paper_model_layers(2), "model5": workload.paper_model_layers(5)}.get(net)
+    blocks = {"model6": workload.resnet_blocks([512] * 4), "r512": workload.resnet_blocks([512] * 2)}.get(net)
+    times = {(64, 32): t64x32, (64, 64): t64x64, (128, 32): t128x32, (96, 64): t96x64}
+    plan = launches(d, d, "bf16", batch, layers, blocks, "paper")
+    assert {(r.rows, r.cols, r.parts) for r in plan} == {min(times, key=times.get) + (4,)}, plan
+
+
 # Streams timed both ways, core = buffer = d (us: one batch / a batch per length and boundary kind)
 STREAMS = [
     (1, "fp8", 13, 39, 4, 146, 190), (1, "bf16", 13, 39, 8, 327, 402), (4, "bf16", 13, 65, 8, 920, 1165),
